@@ -485,15 +485,16 @@ def measure_serial(job, steps):
             if pss == "wgrad":
                 d = job.fc_desc if lname == "fc" else [L for L in job.layers if L["name"] == lname][0]["desc"]
                 nw = d.k * d.r * d.s * d.c
-                sname, sms = c["sum"]
-                splits = int(sname.split("<")[1].rstrip(">"))
-                passes["split_sum"][0] += sms
-                passes["split_sum"][1] += 1
-                passes["split_sum"][2] += 4 * nw * splits + (4 * nw if splits > 1 else 0)
-                passes["update"][0] += c["update_ms"]
-                passes["update"][1] += 1
-                passes["update"][2] += 6 * nw
-                call_ms += sms + c["update_ms"]
+                if c["sum"] is not None:   # short reductions have no passes of their own
+                    sname, sms = c["sum"]
+                    splits = int(sname.split("<")[1].rstrip(">"))
+                    passes["split_sum"][0] += sms
+                    passes["split_sum"][1] += 1
+                    passes["split_sum"][2] += 4 * nw * splits + (4 * nw if splits > 1 else 0)
+                    passes["update"][0] += c["update_ms"]
+                    passes["update"][1] += 1
+                    passes["update"][2] += 6 * nw
+                    call_ms += sms + c["update_ms"]
         e = layer.setdefault((lname, pss), [0, 0.0, ops, nbytes])
         e[0] += 1
         e[1] += call_ms

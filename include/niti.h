@@ -318,7 +318,8 @@ size_t niti_stats_bytes(void);
  *                       every niti_gemm_fwd / niti_conv_fwd /
  *                       niti_conv_bwd_data(_packed) call;
  *   NITI_TIMING_WGRAD   the weight-gradient contraction kernel of every
- *                       niti_conv_bwd_weight call;
+ *                       niti_conv_bwd_weight call (for short reductions,
+ *                       which have no passes of their own, the whole call);
  *   NITI_TIMING_KERNEL  every contraction kernel launch alone (the main
  *                       implicit-GEMM or weight-gradient kernel), labelled
  *                       with the kernel and its template arguments;

@@ -11,6 +11,8 @@ namespace {
 
 constexpr int kThreads = 256;
 
+constexpr int kStatsGrid = 768;   // most workgroups of a launch whose workgroups read the call's statistics
+
 inline int grid_for(int64_t n, int per_thread = 4, int cap = 2048) {
     int64_t g = (n + (int64_t)kThreads * per_thread - 1) / ((int64_t)kThreads * per_thread);
     if (g < 1) g = 1;
@@ -290,10 +292,11 @@ __global__ void round_i32_kernel(const int32_t* x, int8_t* y, int64_t n, int bp_
 
 // Discrete update, the finishing launch of its call:
 // g = round(g32, max(0, B(g32) - mu)); w <- clamp(w - g).
-__global__ void update_kernel(int8_t* __restrict__ w, const int32_t* __restrict__ g32, int64_t n, int mu, int mode,
+template <int RM>
+__global__ void update_kernel(int8_t* __restrict__ w, const int32_t* __restrict__ g32, int64_t n, int mu,
                               niti_stats* st, uint32_t static_flags) {
     const int bp = block_bp(shared_call_state(st).mx, mu);
-    RoundK rk = make_round(bp, mode);
+    RoundK rk = make_round(bp, RM);
     sr_key_recorded(rk, st);
     const int64_t stride = (int64_t)gridDim.x * blockDim.x;
     const int64_t tid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -315,14 +318,7 @@ __global__ void update_kernel(int8_t* __restrict__ w, const int32_t* __restrict_
             const int64_t q = q0 + j * stride;
             if (q >= nq) continue;
             const int32_t gv[4] = {g[j].x, g[j].y, g[j].z, g[j].w};
-            uint32_t out = 0;
-#pragma unroll
-            for (int e = 0; e < 4; e++) {
-                int v = (int)(int8_t)(wv[j] >> (8 * e)) - (int)round_i32_at(gv[e], rk, (uint64_t)(4 * q + e));
-                v = v > 127 ? 127 : (v < -127 ? -127 : v);
-                out |= (uint32_t)(uint8_t)v << (8 * e);
-            }
-            ((uint32_t*)w)[q] = out;
+            ((uint32_t*)w)[q] = update_word<RM>(wv[j], gv, rk, (uint64_t)(4 * q));
         }
     }
     for (int64_t i = 4 * nq + tid; i < n; i += stride) {
@@ -924,7 +920,7 @@ hipError_t max_abs_i32(const int32_t* x, int64_t n, niti_stats* st, hipStream_t 
 
 hipError_t round_i32_run(const int32_t* x, int8_t* y, int64_t n, int bp, int target, int mode,
                          niti_stats* st, ExpArgs ex, hipStream_t s) {
-    hipLaunchKernelGGL(round_i32_kernel, dim3(grid_for(n, 8)), dim3(kThreads), 0, s, x, y, n, bp,
+    hipLaunchKernelGGL(round_i32_kernel, dim3(grid_for(n, 8, st ? kStatsGrid : 2048)), dim3(kThreads), 0, s, x, y, n, bp,
                        target, mode, st, ex);
     return hipGetLastError();
 }
@@ -977,8 +973,14 @@ hipError_t reduce_max_run(const int32_t* part, int splits, int32_t* g32, int64_t
 
 hipError_t update_run(int8_t* w, const int32_t* g32, int64_t n, int mu, int mode, niti_stats* st,
                       uint32_t static_flags, hipStream_t s) {
-    hipLaunchKernelGGL(update_kernel, dim3(grid_for(n, 8)), dim3(kThreads), 0, s, w, g32, n, mu, mode, st,
-                       static_flags);
+    // every workgroup reads the one statistics line, where requests queue
+    const dim3 grid(grid_for(n, 8, kStatsGrid));
+    if (mode == NITI_ROUND_SR)
+        hipLaunchKernelGGL(update_kernel<NITI_ROUND_SR>, grid, dim3(kThreads), 0, s, w, g32, n, mu, st, static_flags);
+    else if (mode == NITI_ROUND_RTN)
+        hipLaunchKernelGGL(update_kernel<NITI_ROUND_RTN>, grid, dim3(kThreads), 0, s, w, g32, n, mu, st, static_flags);
+    else
+        hipLaunchKernelGGL(update_kernel<NITI_ROUND_PSR>, grid, dim3(kThreads), 0, s, w, g32, n, mu, st, static_flags);
     return hipGetLastError();
 }
 

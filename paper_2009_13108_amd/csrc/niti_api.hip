@@ -542,6 +542,19 @@ niti_status niti_conv_bwd_weight(const niti_conv_desc* d, const int8_t* x, const
         p.x = xpad;
     }
     p.part = part;
+    // Short reductions: contraction, maximum and update in two launches.
+    if (wgrad_small_eligible(p)) {
+        const int t = timing_begin(NITI_TIMING_WGRAD, strm);
+        e = wgrad_small_run(p, w, g32_out, mu, mode, stats, acc_flags(npix), strm);
+        timing_end(t, strm);
+        return hip_status(e);
+    }
+    if (!g32_out && !ws_.tap && wgrad_twice_eligible(p, plan)) {
+        const int t = timing_begin(NITI_TIMING_WGRAD, strm);
+        e = wgrad_twice_run(p, plan, w, mu, mode, stats, acc_flags(npix), strm);
+        timing_end(t, strm);
+        return hip_status(e);
+    }
     const int tix = timing_begin(NITI_TIMING_WGRAD, strm);
     if (ws_.tap)
         e = wgrad_tap_run(p, plan, strm);

@@ -140,6 +140,31 @@ __device__ __forceinline__ int8_t round_i32_at(int32_t v, const RoundK& k, uint6
     return (int8_t)(v < 0 ? -q : q);
 }
 
+// Discrete update of four packed weights (Section 3.3): w <- w - round(g),
+// held to [-127, 127], in rounding mode RM (a template argument: the mode test
+// per element cost as much as the rounding); idx keys the first one's
+// stochastic draw.
+template <int RM>
+__device__ __forceinline__ uint32_t update_word(uint32_t w, const int32_t (&g)[4], const RoundK& k, uint64_t idx) {
+    uint32_t out = 0;
+#pragma unroll
+    for (int e = 0; e < 4; e++) {
+        const uint32_t x = mag32(g[e]);
+        uint32_t q;
+        if (RM == NITI_ROUND_SR)
+            q = round_sr_mag32(x, k, idx + e);
+        else if (RM == NITI_ROUND_RTN)
+            q = min((x >> k.bp) + (k.bp ? (x >> (k.bp - 1)) & 1u : 0u), 127u);
+        else
+            q = round_psr_mag_fast(x, k);
+        const int32_t sgn = g[e] >> 31;
+        int v = (int)(int8_t)(w >> (8 * e)) - (((int32_t)q ^ sgn) - sgn);
+        v = min(max(v, -127), 127);
+        out |= (uint32_t)(uint8_t)v << (8 * e);
+    }
+    return out;
+}
+
 __device__ __forceinline__ int8_t round_i64(int64_t v, const RoundK& k) {
     uint64_t m = v < 0 ? 0ull - (uint64_t)v : (uint64_t)v;
     int32_t q = (int32_t)round_mag64(m, k);

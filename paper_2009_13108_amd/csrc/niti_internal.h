@@ -126,6 +126,16 @@ WgradPlan wgrad_plan(int64_t K, int64_t ncol, int64_t npix, int64_t groups);
 hipError_t wgrad_run(WgradProblem& p, const WgradPlan& plan, hipStream_t stream);
 bool wgrad_dma_eligible(const WgradProblem& p);
 hipError_t wgrad_dma_run(WgradProblem& p, const WgradPlan& plan, hipStream_t stream);
+// The whole call (contraction, maximum, update) of a one-range plan in two
+// launches of the DMA kernel, without g32 in memory (wgrad_dma.hip).
+bool wgrad_twice_eligible(const WgradProblem& p, const WgradPlan& plan);
+hipError_t wgrad_twice_run(WgradProblem& p, const WgradPlan& plan, int8_t* w, int mu, int mode, niti_stats* st,
+                           uint32_t static_flags, hipStream_t stream);
+// The whole call of a small fully-connected layer in two launches
+// (wgrad_small.hip); g32 (or NULL) receives the int32 gradient.
+bool wgrad_small_eligible(const WgradProblem& p);
+hipError_t wgrad_small_run(WgradProblem& p, int8_t* w, int32_t* g32, int mu, int mode, niti_stats* st,
+                           uint32_t static_flags, hipStream_t stream);
 // 3x3 filters, C and K multiples of 64: all nine taps of a channel chunk per
 // workgroup (wgrad_tap.hip).
 bool wgrad_tap_eligible(const WgradProblem& p);

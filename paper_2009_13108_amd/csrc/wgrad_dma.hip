@@ -18,6 +18,11 @@
 // Each workgroup reduces one pixel range for one output tile and stores the
 // partial tile to its own slice; a bandwidth pass sums the slices.
 //
+// One pixel range (a fully-connected layer's batch): the contraction is run
+// twice instead, once for the tensor maximum and once to round and update the
+// weights in its epilogue, and g32 never goes through memory
+// (wgrad_twice_run).
+//
 // Window mode (few channels, S*C <= 64): x is a zero-padded copy of the
 // input, and a filter row (r) is one window of Lw bytes (S pixels and zero
 // columns past them), so column col = r*Lw + j of X is x_pad at pixel row
@@ -82,27 +87,25 @@ __device__ __forceinline__ v4i tr_fragment(const int8_t* region, int p0, int cba
     return r;
 }
 
-// Workgroup order.  Workgroups go to the eight XCDs (each with its own L2)
-// in turn by linear index, so workgroup L runs on XCD L % 8.  The work items
-// (split, tile), tile fastest, are cut into eight equal consecutive runs, one
-// per XCD: the output tiles of one pixel range, which read the same input
-// pixels (shifted per tap) and the same errors, then mostly share an XCD and
-// meet in its L2, and every XCD gets the same amount of work.
-template <int TBK, int TBC, int NS>
-__global__ __launch_bounds__(256, 1) void wgrad_dma_kernel(WgradProblem P, int tiles_c, int tiles_k, int splits) {
+// What becomes of a tile (template argument EP): stored as a partial sum;
+// folded into the call's maximum; or, for EP >= 0, rounded in mode EP with the
+// call's shift and subtracted from w.
+constexpr int kStore = -2;
+constexpr int kMaxOnly = -1;
+struct WgradFinish {
+    int8_t* w;
+    niti_stats* st;
+    int mu;
+    uint32_t static_flags;
+};
+
+template <int TBK, int TBC, int NS, int EP>
+__device__ __forceinline__ void wgrad_tile(const WgradProblem& P, int8_t* lds, int split, int c0, int k0,
+                                           const WgradFinish& fin, const RoundK& rk, uint32_t& tmax) {
     using T = WCfg<TBK, TBC, NS>;
-    extern __shared__ __attribute__((aligned(1024))) int8_t lds[];
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int wk = wave & 1, wc = wave >> 1;
-    const int ntiles = tiles_c * tiles_k;
-    const int per_xcd = (ntiles * splits + 7) / 8;
-    const int item = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
-    if ((blockIdx.x >> 3) >= per_xcd || item >= ntiles * splits) return;
-    const int split = item / ntiles;
-    const int tile = item - split * ntiles;
-    const int c0 = (tile % tiles_c) * TBC;
-    const int k0 = (tile / tiles_c) * TBK;
     const int pbeg = split * P.chunk;
     const int pend = min(P.npix, pbeg + P.chunk);
     const int nsteps = pend > pbeg ? (pend - pbeg + PIX - 1) / PIX : 0;
@@ -200,6 +203,24 @@ __global__ __launch_bounds__(256, 1) void wgrad_dma_kernel(WgradProblem P, int t
 
 #pragma unroll
     for (int s = 0; s < NS - 1; s++) issue();
+    // The weights this lane updates (16 consecutive columns per fragment, see
+    // the epilogue), on their way during the contraction.
+    uint4 wold[EP >= 0 ? T::FC : 1][T::FK];
+    auto weight_at = [&](int a, int b, int& k, int& col) {
+        k = k0 + wk * T::WTK + b * 32 + (lane & 31);
+        col = c0 + wc * T::WTC + a * 32 + 16 * (lane >> 5);
+        return k < P.K && col < P.ncol;   // ncol % 16 == 0
+    };
+    if constexpr (EP >= 0) {
+#pragma unroll
+        for (int a = 0; a < T::FC; a++)
+#pragma unroll
+            for (int b = 0; b < T::FK; b++) {
+                int k, col;
+                wold[a][b] = weight_at(a, b, k, col) ? *(const uint4*)(fin.w + (int64_t)k * P.ncol + col)
+                                                     : make_uint4(0, 0, 0, 0);
+            }
+    }
     for (int it = 0; it < nsteps; it++) {
         wait_vm<(NS - 2) * T::IPW>();
         __builtin_amdgcn_s_barrier();
@@ -222,6 +243,49 @@ __global__ __launch_bounds__(256, 1) void wgrad_dma_kernel(WgradProblem P, int t
     }
     wait_vm<0>();
 
+    if constexpr (EP == kMaxOnly) {
+        // columns and channels past the edge accumulated zeros
+#pragma unroll
+        for (int a = 0; a < T::FC; a++)
+#pragma unroll
+            for (int b = 0; b < T::FK; b++)
+#pragma unroll
+                for (int e = 0; e < 16; e++) tmax = max(tmax, mag32(acc[a][b][e]));
+        return;
+    }
+    if constexpr (EP >= 0) {
+#pragma unroll
+        for (int b = 0; b < T::FK; b++) {
+            const int k = k0 + wk * T::WTK + b * 32 + (lane & 31);
+#pragma unroll
+            for (int a = 0; a < T::FC; a++) {
+                // The lane holds old weights of sixteen consecutive columns
+                // (lanes 0..31 columns 0..15 of the fragment, lanes 32..63
+                // 16..31); two half-wave swaps (lanes 32..63 of the first
+                // operand with lanes 0..31 of the second) give it the words
+                // its accumulators belong to (word jj: columns 8 jj +
+                // 4 (lane / 32) ..), and the same swaps undo that.
+                const uint4 o = wold[a][b];
+                const auto o02 = __builtin_amdgcn_permlane32_swap(o.x, o.y, false, false);
+                const auto o13 = __builtin_amdgcn_permlane32_swap(o.z, o.w, false, false);
+                const uint32_t ow[4] = {o02[0], o13[0], o02[1], o13[1]};
+                uint32_t nw[4];
+#pragma unroll
+                for (int jj = 0; jj < 4; jj++) {
+                    const int32_t g[4] = {acc[a][b][4 * jj], acc[a][b][4 * jj + 1], acc[a][b][4 * jj + 2],
+                                          acc[a][b][4 * jj + 3]};
+                    const int cl = c0 + wc * T::WTC + a * 32 + 8 * jj + 4 * (lane >> 5);
+                    nw[jj] = update_word<EP>(ow[jj], g, rk, (uint64_t)k * P.ncol + cl);
+                }
+                const auto n02 = __builtin_amdgcn_permlane32_swap(nw[0], nw[2], false, false);
+                const auto n13 = __builtin_amdgcn_permlane32_swap(nw[1], nw[3], false, false);
+                int kw, col;
+                if (weight_at(a, b, kw, col))
+                    *(uint4*)(fin.w + (int64_t)kw * P.ncol + col) = make_uint4(n02[0], n02[1], n13[0], n13[1]);
+            }
+        }
+        return;
+    }
     // acc[a][b] element 4*jj + i: column c0 + wc*WTC + a*32 + 8*jj + 4*(lane/32) + i,
     // channel k0 + wk*WTK + b*32 + lane%32: four consecutive columns per store.
     int32_t* out = P.part + (int64_t)split * P.K * P.ncol;
@@ -254,24 +318,69 @@ __global__ __launch_bounds__(256, 1) void wgrad_dma_kernel(WgradProblem P, int t
     }
 }
 
-template <int TBK, int TBC, int NS>
-hipError_t launch(const WgradProblem& p, const WgradPlan& plan, hipStream_t stream) {
+// Workgroup order.  Workgroups go to the eight XCDs (each with its own L2)
+// in turn by linear index, so workgroup L runs on XCD L % 8.  The work items
+// (split, tile), tile fastest, are cut into eight equal consecutive runs, one
+// per XCD: the output tiles of one pixel range, which read the same input
+// pixels (shifted per tap) and the same errors, then mostly share an XCD and
+// meet in its L2, and every XCD gets the same amount of work.  A grid smaller
+// than the item count strides over its XCD's run.
+template <int TBK, int TBC, int NS, int EP>
+__global__ __launch_bounds__(256, 1) void wgrad_dma_kernel(WgradProblem P, int tiles_c, int tiles_k, int splits,
+                                                           WgradFinish fin) {
+    extern __shared__ __attribute__((aligned(1024))) int8_t lds[];
+    const int ntiles = tiles_c * tiles_k;
+    const int per_xcd = (ntiles * splits + 7) / 8;
+    int slot = 0;
+    RoundK rk{};
+    if constexpr (EP == kMaxOnly) {
+        slot = call_slot(fin.st);
+        begin_call(fin.st, slot, -1);
+    }
+    if constexpr (EP >= 0) {
+        rk = make_round(block_bp(shared_call_state(fin.st, lds).mx, fin.mu), EP);
+        sr_key_recorded(rk, fin.st);
+    }
+    uint32_t tmax = 0;
+    for (int s = blockIdx.x >> 3; s < per_xcd; s += gridDim.x >> 3) {
+        const int item = (blockIdx.x & 7) * per_xcd + s;
+        if (item >= ntiles * splits) break;
+        const int split = item / ntiles;
+        const int tile = item - split * ntiles;
+        wgrad_tile<TBK, TBC, NS, EP>(P, lds, split, (tile % tiles_c) * TBC, (tile / tiles_c) * TBK, fin, rk, tmax);
+        if constexpr (EP != kStore) __syncthreads();   // the ring is free for the next tile
+    }
+    if constexpr (EP == kMaxOnly) {
+        const uint64_t snap = max_snapshot(fin.st, slot);
+        block_publish_max32(fin.st, slot, tmax, (uint32_t*)lds, snap);   // magnitudes <= 2^31
+    }
+    if constexpr (EP >= 0) {
+        if (is_finisher()) finish_call(fin.st, fin.mu, ExpArgs{nullptr, nullptr, nullptr}, fin.static_flags, 0);
+    }
+}
+
+template <int TBK, int TBC, int NS, int EP>
+hipError_t launch(const WgradProblem& p, const WgradPlan& plan, hipStream_t stream, WgradFinish fin = WgradFinish{}) {
     using T = WCfg<TBK, TBC, NS>;
     static bool attr_done = false;
     if (!attr_done) {
-        hipError_t e = hipFuncSetAttribute((const void*)wgrad_dma_kernel<TBK, TBC, NS>,
+        hipError_t e = hipFuncSetAttribute((const void*)wgrad_dma_kernel<TBK, TBC, NS, EP>,
                                            hipFuncAttributeMaxDynamicSharedMemorySize, T::LDS);
         if (e != hipSuccess) return e;
         attr_done = true;
     }
     const int tc = ((p.win ? p.ncol_w : p.ncol) + TBC - 1) / TBC;
     const int tk = (p.K + TBK - 1) / TBK;
-    const int64_t grid = (int64_t)8 * (((int64_t)tc * tk * plan.splits + 7) / 8);
+    int64_t grid = (int64_t)8 * (((int64_t)tc * tk * plan.splits + 7) / 8);
+    // Each workgroup of a call's maximum or update launch goes to the one
+    // statistics line, where requests queue at several nanoseconds each: two
+    // per CU and no more.
+    if (EP != kStore && grid > 512) grid = 512;
     const int t = timing_on() ? timing_begin(NITI_TIMING_KERNEL, stream,
                                              kernel_label("wgrad_dma_kernel<%d,%d,%d>", TBK, TBC, NS))
                               : -1;
-    hipLaunchKernelGGL((wgrad_dma_kernel<TBK, TBC, NS>), dim3((unsigned)grid), dim3(256), T::LDS, stream, p, tc, tk,
-                       plan.splits);
+    hipLaunchKernelGGL((wgrad_dma_kernel<TBK, TBC, NS, EP>), dim3((unsigned)grid), dim3(256), T::LDS, stream, p, tc, tk,
+                       plan.splits, fin);
     timing_end(t, stream);
     return hipGetLastError();
 }
@@ -286,8 +395,34 @@ bool wgrad_dma_eligible(const WgradProblem& p) {
 
 hipError_t wgrad_dma_run(WgradProblem& p, const WgradPlan& plan, hipStream_t stream) {
     p.chunk = plan.chunk;
-    if (plan.tbk == 64) return launch<64, 128, 4>(p, plan, stream);
-    return launch<128, 128, 4>(p, plan, stream);
+    if (plan.tbk == 64) return launch<64, 128, 4, kStore>(p, plan, stream);
+    return launch<128, 128, 4, kStore>(p, plan, stream);
+}
+
+// Running the contraction again costs its 2 npix operations per weight once
+// more and saves the int32 gradient's round trips: 12 bytes per weight
+// (written, read for the maximum, read for the update).  At this kernel's
+// ~1 POPS against ~5 TB/s that is even near 1000 samples; 512 leaves a margin.
+// 4096 -> 4096, 128 samples (16.8 M weights): 61.0 us as contraction, maximum
+// and update, 31.4 us this way (13.0 + 18.5; the update's share is bound by
+// the ~14 vector instructions per weight next to the 33.5 MB it moves).
+bool wgrad_twice_eligible(const WgradProblem& p, const WgradPlan& plan) {
+    return plan.splits == 1 && !p.win && p.npix <= 512 && wgrad_dma_eligible(p);
+}
+
+hipError_t wgrad_twice_run(WgradProblem& p, const WgradPlan& plan, int8_t* w, int mu, int mode, niti_stats* st,
+                           uint32_t static_flags, hipStream_t stream) {
+    p.chunk = plan.chunk;
+    // Three stages: the whole ring of a batch of 128 is in flight at once, and
+    // the 48 KB let three workgroups share a CU instead of two.
+    const WgradFinish fin{w, st, mu, static_flags};
+#define NITI_TWICE(EP) (plan.tbk == 64 ? launch<64, 128, 3, EP>(p, plan, stream, fin) : launch<128, 128, 3, EP>(p, plan, stream, fin))
+    hipError_t e = NITI_TWICE(kMaxOnly);
+    if (e != hipSuccess) return e;
+    if (mode == NITI_ROUND_SR) return NITI_TWICE(NITI_ROUND_SR);
+    if (mode == NITI_ROUND_RTN) return NITI_TWICE(NITI_ROUND_RTN);
+    return NITI_TWICE(NITI_ROUND_PSR);
+#undef NITI_TWICE
 }
 
 }  // namespace niti
