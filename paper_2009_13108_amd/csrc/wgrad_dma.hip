@@ -57,13 +57,14 @@ struct WCfg {
     static constexpr int XBLK = TBC * PIX / 1024;      // 1 KiB blocks of the X tile per stage
     static constexpr int DBLK = TBK * PIX / 1024;      // blocks of the dy tile
     static constexpr int BLOCKS = XBLK + DBLK;
-    static constexpr int IPW = BLOCKS / 4;
+    static constexpr int XPW = XBLK / 4, DPW = DBLK / 4;   // blocks a wave loads per stage
+    static constexpr int IPW = XPW + DPW;
     static constexpr int XBYTES = TBC * PIX;
     static constexpr int STAGE = (TBC + TBK) * PIX;
     static constexpr int LDS = NS * STAGE;
     static constexpr int WTK = TBK / 2, WTC = TBC / 2;  // 2 x 2 waves
     static constexpr int FK = WTK / 32, FC = WTC / 32;
-    static_assert(BLOCKS % 4 == 0, "blocks per wave");
+    static_assert(XBLK % 4 == 0 && DBLK % 4 == 0, "blocks per wave");
 };
 
 // One 32 x 32-pixel fragment from a pixel-major region with RB-byte rows:
@@ -116,79 +117,95 @@ __device__ __forceinline__ void wgrad_tile(const WgradProblem& P, int8_t* lds, i
     const u32x4 drs = raw_rsrc(P.dy, (uint32_t)P.dy_bytes);
     const uint32_t lds0 = lds_address(lds);
 
-    // Per load instruction: pixel row within the stage, and the column /
-    // channel this lane's chunk covers (fixed over the reduction).
-    int prow[T::IPW];
-    int tdh[T::IPW], tdw[T::IPW];   // X: tap displacement (r - ph, s - pw); dy: unused
-    uint32_t toff[T::IPW];          // X: channel offset c; dy: channel k
-    bool cok[T::IPW];
+    // Loads of a wave and stage: XPW blocks of the X tile (8 pixels x 128
+    // bytes) and DPW of the dy tile.  A lane keeps the buffer offset of its
+    // 16 bytes and moves it by PIX pixels per stage with adds and two wraps
+    // (row, image) instead of decoding the pixel again: the address work
+    // was ~200 vector instructions per stage against 8 MFMAs, half of the
+    // waves did all of it for X, and it bounded the kernel.  Pixels at or past
+    // npix need no test: their dy offsets lie past the buffer's end and load
+    // zeros (a split's range ends on a stage, or at npix).
+    uint32_t xoff[T::XPW], doff[T::DPW];
+    int ih[T::XPW], iw[T::XPW], lim_h[T::XPW], lim_w[T::XPW];   // input position of the tap, and its wraps
+    const bool lin = !P.win && P.R == 1 && P.S == 1 && P.sh == 1 && P.sw == 1 && P.ph == 0 && P.pw == 0;
+    const int pq = P.P * P.Q;
+    const int dn = PIX / pq, drem = PIX - dn * pq, doh = drem / P.Q, dow = drem - doh * P.Q;
+    const uint32_t off_step = lin ? (uint32_t)(PIX * P.C) : (uint32_t)(((dn * P.H + doh * P.sh) * P.W + dow * P.sw) * P.C);
+    const uint32_t wrap_w = (uint32_t)((P.sh * P.W - P.Q * P.sw) * P.C);
+    const uint32_t wrap_h = (uint32_t)((P.H - P.P * P.sh) * P.W * P.C);
+    const int step_w = dow * P.sw, step_h = doh * P.sh, span_w = P.Q * P.sw, span_h = P.P * P.sh;
 #pragma unroll
-    for (int i = 0; i < T::IPW; i++) {
-        const int blk = wave * T::IPW + i;   // uniform
-        if (blk < T::XBLK) {
-            // 128-byte rows: 8 pixels x 8 chunks per block
-            const int p = blk * 8 + (lane >> 3);
-            const int chunk = (lane & 7) ^ swz<TBC>(p);
-            const int col = c0 + 16 * chunk;
-            prow[i] = p;
-            if (P.win) {
-                cok[i] = col < P.ncol_w;
-                const int cc = cok[i] ? col : 0;
-                const int r = cc / P.Lw;
-                tdh[i] = 0;
-                tdw[i] = 0;
-                toff[i] = (uint32_t)(r * P.W * P.C + (cc - r * P.Lw));
-            } else {
-                cok[i] = col < P.ncol;
-                const int cc = cok[i] ? col : 0;
-                const int r = (int)fdiv((uint32_t)cc, P.div_l);
-                const int jj = cc - r * P.L;
-                const int s = (int)fdiv((uint32_t)jj, P.div_c);
-                tdh[i] = r - P.ph;
-                tdw[i] = s - P.pw;
-                toff[i] = (uint32_t)(jj - s * P.C);
-            }
+    for (int i = 0; i < T::XPW; i++) {
+        const int p = (wave * T::XPW + i) * 8 + (lane >> 3);
+        const int col = c0 + 16 * ((lane & 7) ^ swz<TBC>(p));
+        const bool cok = col < (P.win ? P.ncol_w : P.ncol);
+        const int cc = cok ? col : 0;
+        int tdh = 0, tdw = 0;
+        uint32_t toff;
+        if (P.win) {
+            const int r = cc / P.Lw;
+            toff = (uint32_t)(r * P.W * P.C + (cc - r * P.Lw));
         } else {
-            const int b = blk - T::XBLK;
-            constexpr int PPB = 1024 / TBK;          // pixels per block
-            constexpr int CPR = TBK / 16;            // chunks per row
-            const int p = b * PPB + lane / CPR;
-            const int chunk = (lane % CPR) ^ swz<TBK>(p);
-            const int k = k0 + 16 * chunk;
-            prow[i] = p;
-            cok[i] = k < P.K;
-            tdh[i] = 0;
-            tdw[i] = 0;
-            toff[i] = (uint32_t)k;
+            const int r = (int)fdiv((uint32_t)cc, P.div_l);
+            const int jj = cc - r * P.L;
+            const int s = (int)fdiv((uint32_t)jj, P.div_c);
+            tdh = r - P.ph;
+            tdw = s - P.pw;
+            toff = (uint32_t)(jj - s * P.C);
         }
+        const int pix = pbeg + p;
+        const int n = (int)fdiv((uint32_t)pix, P.div_pq);
+        const int rem = pix - n * pq;
+        const int oh = (int)fdiv((uint32_t)rem, P.div_q);
+        const int ow = rem - oh * P.Q;
+        ih[i] = oh * P.sh + tdh;
+        iw[i] = ow * P.sw + tdw;
+        xoff[i] = (uint32_t)(((n * P.H + ih[i]) * P.W + iw[i]) * P.C) + toff;
+        lim_h[i] = span_h + tdh;
+        lim_w[i] = span_w + tdw;
+        if (!cok) {   // a column past the edge: never inside
+            if (P.win || lin)
+                xoff[i] = kOOB;
+            else
+                ih[i] = -(1 << 30), lim_h[i] = 1 << 30;
+        }
+    }
+    constexpr int PPB = 1024 / TBK, CPR = TBK / 16;   // dy: pixels per block, chunks per row
+#pragma unroll
+    for (int i = 0; i < T::DPW; i++) {
+        const int p = (wave * T::DPW + i) * PPB + lane / CPR;
+        const int k = k0 + 16 * ((lane % CPR) ^ swz<TBK>(p));
+        doff[i] = k < P.K ? (uint32_t)(pbeg + p) * (uint32_t)P.K + (uint32_t)k : kOOB;
     }
 
     int next = 0;
+    const uint32_t xdst = lds0 + (uint32_t)(wave * T::XPW) * 1024u;
+    const uint32_t ddst = lds0 + (uint32_t)(T::XBLK + wave * T::DPW) * 1024u;
+    // kOOB offsets may move too: at most 2^31 - 1 bytes below them are valid,
+    // and a stage count times the step stays below 2^31 (wgrad_dma_eligible).
     auto issue = [&]() {
-        const uint32_t st = lds0 + (uint32_t)((next % NS) * T::STAGE);
-        const int pb = pbeg + next * PIX;
+        const uint32_t slot = (uint32_t)((next % NS) * T::STAGE);
 #pragma unroll
-        for (int i = 0; i < T::IPW; i++) {
-            const int blk = wave * T::IPW + i;
-            const int pix = pb + prow[i];
-            const bool pok = next < nsteps && pix < pend && cok[i];
-            uint32_t off = kOOB;
-            if (blk < T::XBLK) {
-                if (pok) {
-                    const int n = (int)fdiv((uint32_t)pix, P.div_pq);
-                    const int rem = pix - n * P.P * P.Q;
-                    const int oh = (int)fdiv((uint32_t)rem, P.div_q);
-                    const int ow = rem - oh * P.Q;
-                    const int ih = oh * P.sh + tdh[i];
-                    const int iw = ow * P.sw + tdw[i];
-                    if (P.win || ((unsigned)ih < (unsigned)P.H && (unsigned)iw < (unsigned)P.W))
-                        off = (uint32_t)(((n * P.H + ih) * P.W + iw) * P.C) + toff[i];
-                }
-                lds_dma16(xrs, st + blk * 1024, off, 0);
-            } else {
-                if (pok) off = (uint32_t)pix * (uint32_t)P.K + toff[i];
-                lds_dma16(drs, st + blk * 1024, off, 0);
+        for (int i = 0; i < T::XPW; i++) {
+            const bool in = P.win || lin || ((unsigned)ih[i] < (unsigned)P.H && (unsigned)iw[i] < (unsigned)P.W);
+            lds_dma16_at(xrs, xdst, slot + i * 1024, in ? xoff[i] : kOOB, 0);
+            xoff[i] += off_step;
+            if (!lin) {
+                iw[i] += step_w;
+                ih[i] += step_h;
+                const bool ww = iw[i] >= lim_w[i];
+                iw[i] -= ww ? span_w : 0;
+                ih[i] += ww ? P.sh : 0;
+                xoff[i] += ww ? wrap_w : 0u;
+                const bool wh = ih[i] >= lim_h[i];
+                ih[i] -= wh ? span_h : 0;
+                xoff[i] += wh ? wrap_h : 0u;
             }
+        }
+#pragma unroll
+        for (int i = 0; i < T::DPW; i++) {
+            lds_dma16_at(drs, ddst, slot + i * 1024, doff[i], 0);
+            doff[i] += (uint32_t)(PIX * P.K);
         }
         next++;
     };
@@ -342,13 +359,21 @@ __global__ __launch_bounds__(256, 1) void wgrad_dma_kernel(WgradProblem P, int t
         sr_key_recorded(rk, fin.st);
     }
     uint32_t tmax = 0;
+    if constexpr (EP == kStore) {   // one item per workgroup
+        const int item = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
+        if ((blockIdx.x >> 3) >= per_xcd || item >= ntiles * splits) return;
+        const int split = item / ntiles;
+        const int tile = item - split * ntiles;
+        wgrad_tile<TBK, TBC, NS, EP>(P, lds, split, (tile % tiles_c) * TBC, (tile / tiles_c) * TBK, fin, rk, tmax);
+        return;
+    }
     for (int s = blockIdx.x >> 3; s < per_xcd; s += gridDim.x >> 3) {
         const int item = (blockIdx.x & 7) * per_xcd + s;
         if (item >= ntiles * splits) break;
         const int split = item / ntiles;
         const int tile = item - split * ntiles;
         wgrad_tile<TBK, TBC, NS, EP>(P, lds, split, (tile % tiles_c) * TBC, (tile / tiles_c) * TBK, fin, rk, tmax);
-        if constexpr (EP != kStore) __syncthreads();   // the ring is free for the next tile
+        __syncthreads();   // the ring is free for the next tile
     }
     if constexpr (EP == kMaxOnly) {
         const uint64_t snap = max_snapshot(fin.st, slot);
@@ -389,6 +414,12 @@ hipError_t launch(const WgradProblem& p, const WgradPlan& plan, hipStream_t stre
 
 bool wgrad_dma_eligible(const WgradProblem& p) {
     const bool cols = p.win ? (p.Lw % 16 == 0 && p.L % 4 == 0 && p.ph == 0 && p.pw == 0) : p.C % 16 == 0;
+    // The ring runs up to four stages past the last pixel; the offsets it
+    // forms there must not come round to the buffer again.
+    const int64_t over = 5 * PIX;
+    if (p.dy_bytes + over * p.K >= ((int64_t)1 << 31) ||
+        p.x_bytes + (over / ((int64_t)p.P * p.Q) + 2) * p.H * p.W * p.C >= ((int64_t)1 << 31))
+        return false;
     return cols && p.K % 16 == 0 && p.x_bytes > 0 && p.x_bytes < ((int64_t)1 << 31) && p.dy_bytes > 0 &&
            p.dy_bytes < ((int64_t)1 << 31);
 }
