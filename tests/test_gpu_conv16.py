@@ -1,0 +1,57 @@
+"""Convolutions whose channel counts are multiples of 16 but not of 64, or
+that have more than 32 filter taps: the carried-piece load mode of the ring
+kernel, forward and back-propagation, exact against the oracle.  Shapes put
+the pieces of one 64-byte step into one, two or five taps, wrap filter rows
+inside a step, end the reduction inside a step, and cover the largest filter
+the mode takes and one past it."""
+import pytest
+
+import oracle
+from paper_2009_13108_amd import inputs as I
+from paper_2009_13108_amd import niti
+from helpers import dev, host, krsc, nchw, nhwc, same_stats, say
+
+pytestmark = pytest.mark.gpu
+
+CASES = [
+    # n, c, h, w, k, r, s, stride, pad, mode
+    (2, 96, 9, 7, 80, 5, 5, 1, 2, oracle.PSR),
+    (1, 80, 11, 13, 144, 3, 3, 2, 1, oracle.RTN),
+    (3, 48, 8, 8, 96, 3, 3, 1, 0, oracle.PSR),
+    (2, 112, 6, 5, 16, 1, 1, 1, 0, oracle.PSR),
+    (2, 16, 12, 9, 32, 7, 7, 1, 3, oracle.PSR),      # four taps in a step
+    (1, 80, 9, 9, 48, 5, 1, 1, 0, oracle.PSR),       # a filter one pixel wide: a row per step
+    (1, 32, 17, 18, 176, 2, 3, 2, 2, oracle.RTN),
+    (1, 64, 12, 12, 64, 7, 7, 1, 3, oracle.PSR),     # 49 taps over whole 64s
+    (1, 64, 14, 13, 128, 11, 11, 2, 5, oracle.PSR),  # classes of 36 and 30 taps in one launch
+    (1, 16, 20, 18, 16, 16, 16, 1, 0, oracle.PSR),   # the largest filter
+    (1, 16, 20, 18, 16, 17, 3, 1, 0, oracle.PSR),    # one row more: the general kernel
+    (40, 48, 28, 28, 272, 3, 3, 1, 1, oracle.PSR),   # several tiles of every kind
+]
+
+
+@pytest.mark.parametrize("case", CASES)
+def test_sixteen_channel_pieces(case):
+    import torch
+    n, c, h, w, k, r, s, stride, pad, mode = case
+    say("conv16", case)
+    d = oracle.conv_desc(n, c, h, w, k, r, s, stride, pad)
+    gd = niti.ConvDesc.make(n, h, w, c, k, r, s, stride, pad)
+    P, Q = oracle.conv_out_hw(d)
+    x, wt, dy = I.activations(61, (n, c, h, w)), I.weights(62, (k, c, r, s)), I.errors8(63, (n, k, P, Q))
+    mask = I.weights(64, (n, c, h, w))
+    y_exp, _, st_f = oracle.conv_fwd(d, x, wt, relu=True, mode=mode)
+    dx_exp, _, st_b = oracle.conv_bwd_data(d, dy, wt, mode=mode, relu_src=mask)
+    y = torch.empty(gd.y_shape(), dtype=torch.int8, device="cuda")
+    dx = torch.empty(gd.x_shape(), dtype=torch.int8, device="cuda")
+    stats = niti.new_stats(2)
+    ws = niti.new_workspace(max(niti.workspace_bytes(op, gd) for op in (niti.OP_CONV_FWD, niti.OP_CONV_BWD_DATA)))
+    xd, wd, dyd, md = dev(nhwc(x)), dev(krsc(wt)), dev(nhwc(dy)), dev(nhwc(mask))
+    for call in range(2):
+        y.fill_(77)
+        dx.fill_(77)
+        niti.conv_fwd(gd, xd, wd, y, stats, relu=True, mode=mode, stats_index=0, ws=ws)
+        niti.conv_bwd_data(gd, dyd, wd, dx, stats, ws, relu_src=md, mode=mode, stats_index=1)
+        got = niti.read_stats(stats)
+        assert (nchw(host(y)) == y_exp).all() and same_stats(got[0], st_f), call
+        assert (nchw(host(dx)) == dx_exp).all() and same_stats(got[1], st_b), call
