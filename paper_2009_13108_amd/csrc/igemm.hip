@@ -52,25 +52,6 @@ __device__ __forceinline__ Tile locate_tile(const IgemmBatch& b, int t) {
     return r;
 }
 
-// 16 bytes from an address of unknown alignment.
-__device__ __forceinline__ uint4 load16(const int8_t* p) {
-    const uintptr_t a = (uintptr_t)p;
-    if ((a & 15) == 0) return *(const uint4*)p;
-    uint4 v;
-    if ((a & 3) == 0) {
-        const uint32_t* q = (const uint32_t*)p;
-        v.x = q[0]; v.y = q[1]; v.z = q[2]; v.w = q[3];
-        return v;
-    }
-    uint32_t w[4];
-#pragma unroll
-    for (int i = 0; i < 4; i++)
-        w[i] = (uint32_t)(uint8_t)p[4 * i] | ((uint32_t)(uint8_t)p[4 * i + 1] << 8) |
-               ((uint32_t)(uint8_t)p[4 * i + 2] << 16) | ((uint32_t)(uint8_t)p[4 * i + 3] << 24);
-    v.x = w[0]; v.y = w[1]; v.z = w[2]; v.w = w[3];
-    return v;
-}
-
 // Bytes [lo, hi) of a 16-byte window starting at p (0 <= lo <= hi <= 16),
 // zero elsewhere.  Only the valid bytes are touched.
 __device__ __forceinline__ uint4 load16_partial(const int8_t* p, int lo, int hi) {
@@ -83,7 +64,7 @@ __device__ __forceinline__ uint4 load16_partial(const int8_t* p, int lo, int hi)
 
 // Per-thread view of one activation row (one output pixel).
 struct ActRow {
-    const int8_t* base;  // image base + (ih0*W + iw0)*C  (may point before the image)
+    int64_t off;         // offset in act of (image, ih0, iw0): before the tensor for border pixels
     int ih0;             // input row of tap 0
     int jlo, jhi;        // valid byte range of a tap row segment: [-iw0*C, (W-iw0)*C)
     int valid;
@@ -108,7 +89,7 @@ __device__ __forceinline__ void setup_act_rows(const IgemmProblem& P, int tm, Ac
         r.ih0 = ih0;
         r.jlo = -iw0 * P.C;
         r.jhi = (P.W - iw0) * P.C;
-        r.base = P.act + (int64_t)img * P.H * P.W * P.C + ((int64_t)ih0 * P.W + iw0) * P.C;
+        r.off = (int64_t)img * P.H * P.W * P.C + ((int64_t)ih0 * P.W + iw0) * P.C;
         rows[i] = r;
     }
 }
@@ -119,23 +100,25 @@ __device__ __forceinline__ uint4 load_act_piece(const IgemmProblem& P, const Act
     if (!row.valid || r >= P.R || (unsigned)ih >= (unsigned)P.H) return z;
     const int lo = max(row.jlo, j), hi = min(min(row.jhi, P.L), j + 16);
     if (hi <= lo) return z;
-    const int8_t* p = row.base + (int64_t)r * P.W * P.C + j;
-    if (lo == j && hi == j + 16) return load16(p);
+    const int64_t off = row.off + (int64_t)r * P.W * P.C + j;
+    const int8_t* p = P.act + off;
+    if (off >= 0 && off + 16 <= P.act_bytes) {   // inside the tensor: read whole, cut to the valid bytes
+        const uint4 v = load16_any(p);
+        return lo == j && hi == j + 16 ? v : keep_bytes(v, lo - j, hi - j);
+    }
     return load16_partial(p, lo - j, hi - j);
 }
 
 __device__ __forceinline__ uint4 load_wgt_piece(const IgemmProblem& P, int n, int r, int j) {
     uint4 z = make_uint4(0, 0, 0, 0);
     if (n >= P.Nout || r >= P.R || j >= P.L) return z;
-    const int8_t* p = P.wgt + ((int64_t)n * P.R + r) * P.L + j;
-    if (j + 16 <= P.L) return load16(p);
-    return load16_partial(p, 0, P.L - j);
-}
-
-// (r, j) of the 16-byte piece at K offset kk (uniform across the block).
-__device__ __forceinline__ void split_k(const IgemmProblem& P, int kk, int& r, int& j) {
-    r = kk / P.Lpad;
-    j = kk - r * P.Lpad;
+    const int64_t off = ((int64_t)n * P.R + r) * P.L + j;
+    const int8_t* p = P.wgt + off;
+    if (off + 16 <= P.wgt_bytes) {
+        const uint4 v = load16_any(p);
+        return j + 16 <= P.L ? v : keep_bytes(v, 0, P.L - j);
+    }
+    return load16_partial(p, 0, min(16, P.L - j));
 }
 
 template <int TBM, int TBN>
@@ -172,43 +155,50 @@ __device__ __forceinline__ void run_tile(const IgemmProblem& P, int tm, int tn, 
 #pragma unroll
             for (int e = 0; e < 16; e++) acc[a][b][e] = 0;
 
+    // Loads run PF steps ahead through registers: four steps for 64 x 64
+    // tiles, so that a step does not wait a memory round trip; one for larger
+    // tiles, where a second would cost a wavefront per SIMD (2912 x 11248 x
+    // 624: 107 us with one, 116 with two).  LDS holds two steps, so one
+    // barrier per step is enough.
+    constexpr int PF = TBM + TBN <= 128 ? 4 : 1;
     const int nk = (P.Ktot + BK - 1) / BK;
-    uint4 ra[PA], rb[PB];
-
-    auto gload = [&](int kt) {
-        const int kk = kt * BK + piece * 16;
-        int r, j;
-        split_k(P, kk, r, j);
+    uint4 ra[PF][PA], rb[PF][PB];
+    // (r, j) of this thread's 16-byte piece at the next step to load, moved by
+    // BK bytes per step with one carry.
+    const int lp = max(P.Lpad, 1);   // 0 for an empty reduction (no steps)
+    int kk = piece * 16;
+    int lr = kk / lp, lj = kk - lr * lp;
+    const int step_r = BK / lp, step_j = BK - step_r * lp;
+    auto gload = [&](uint4 (&a)[PA], uint4 (&b)[PB]) {
 #pragma unroll
         for (int i = 0; i < PA; i++) {
             const int n = tn * TBN + ((threadIdx.x + NTHREADS * i) >> 2);
-            ra[i] = kk < P.Ktot ? load_wgt_piece(P, n, r, j) : make_uint4(0, 0, 0, 0);
+            a[i] = kk < P.Ktot ? load_wgt_piece(P, n, lr, lj) : make_uint4(0, 0, 0, 0);
         }
 #pragma unroll
         for (int i = 0; i < PB; i++)
-            rb[i] = kk < P.Ktot ? load_act_piece(P, rows[i], r, j) : make_uint4(0, 0, 0, 0);
+            b[i] = kk < P.Ktot ? load_act_piece(P, rows[i], lr, lj) : make_uint4(0, 0, 0, 0);
+        kk += BK;
+        lr += step_r;
+        lj += step_j;
+        if (lj >= lp) {
+            lj -= lp;
+            ++lr;
+        }
     };
-    auto sstore = [&](int buf) {
+    auto sstore = [&](int buf, const uint4 (&a)[PA], const uint4 (&b)[PB]) {
 #pragma unroll
         for (int i = 0; i < PA; i++) {
             const int row = (threadIdx.x + NTHREADS * i) >> 2;
-            *(uint4*)&sm.a[buf][row * PITCH + piece * 16] = ra[i];
+            *(uint4*)&sm.a[buf][row * PITCH + piece * 16] = a[i];
         }
 #pragma unroll
         for (int i = 0; i < PB; i++) {
             const int row = (threadIdx.x + NTHREADS * i) >> 2;
-            *(uint4*)&sm.b[buf][row * PITCH + piece * 16] = rb[i];
+            *(uint4*)&sm.b[buf][row * PITCH + piece * 16] = b[i];
         }
     };
-
-    if (nk > 0) {
-        gload(0);
-        sstore(0);
-    }
-    __syncthreads();
-    for (int kt = 0; kt < nk; kt++) {
-        const int buf = kt & 1;
-        if (kt + 1 < nk) gload(kt + 1);
+    auto step = [&](int buf) {
 #pragma unroll
         for (int ks = 0; ks < 2; ks++) {
             const int koff = ks * 32 + (lane >> 5) * 16;
@@ -229,9 +219,22 @@ __device__ __forceinline__ void run_tile(const IgemmProblem& P, int tm, int tn, 
                 for (int b = 0; b < FM; b++)
                     acc[a][b] = __builtin_amdgcn_mfma_i32_32x32x32_i8(fa[a], fb[b], acc[a][b], 0, 0, 0);
         }
-        if (kt + 1 < nk) sstore(buf ^ 1);
-        __syncthreads();
+    };
+#pragma unroll
+    for (int u = 0; u < PF; u++)
+        if (u < nk) gload(ra[u], rb[u]);
+    for (int k0 = 0; k0 < nk; k0 += PF) {
+#pragma unroll
+        for (int u = 0; u < PF; u++) {
+            if (k0 + u >= nk) break;
+            const int buf = PF == 1 ? (k0 & 1) : (u & 1);
+            sstore(buf, ra[u], rb[u]);   // the buffer's last readers passed the previous step's barrier
+            if (k0 + u + PF < nk) gload(ra[u], rb[u]);
+            __syncthreads();
+            step(buf);
+        }
     }
+    __syncthreads();   // the buffers are free for the next tile
 
     // Epilogue.  acc[a][b] element 4*jj + i sits at channel
     // n = tile_n + wn*WTN + a*32 + 8*jj + 4*(lane/32) + i and pixel
@@ -375,6 +378,13 @@ hipError_t launch_igemm(IgemmBatch& b, IgemmCtl ctl, hipStream_t stream) {
 
 namespace {
 
+// 64 x 64 tiles below one 128 x 128 tile per CU: four times the workgroups,
+// and loads four steps ahead.  Measured in us at 64 / 256 / 512 as the limit:
+// 1000 x 1500 x 1111 (96 tiles of 128) 35.5 / 21.9 / 21.9; a 7x7 layer of 36
+// channels (training pass) 145 / 104 / 104; 6000 x 700 x 333 (282 tiles)
+// 29.8 / 24.5 / 31.5.
+constexpr int64_t kSmallTiles = 256;
+
 hipError_t igemm_dispatch(IgemmBatch& b, IgemmCtl ctl, hipStream_t stream) {
     // Stochastic rounding keys each draw by the element's offset in the
     // output, which only this kernel's epilogue carries.
@@ -388,12 +398,10 @@ hipError_t igemm_dispatch(IgemmBatch& b, IgemmCtl ctl, hipStream_t stream) {
         maxM = b.p[i].M > maxM ? b.p[i].M : maxM;
         maxN = b.p[i].Nout > maxN ? b.p[i].Nout : maxN;
     }
-    // Small problems (a classifier head's back-propagation) get 64 x 64
-    // tiles, so that more than a handful of CUs take part.
     int64_t tiles128 = 0;
     for (int i = 0; i < b.nprob; i++)
         tiles128 += (int64_t)((b.p[i].M + 127) / 128) * ((b.p[i].Nout + 127) / 128);
-    if (tiles128 < 64) return launch_igemm<64, 64>(b, ctl, stream);
+    if (tiles128 < kSmallTiles) return launch_igemm<64, 64>(b, ctl, stream);
     (void)maxM;
     if (maxN <= 64) return launch_igemm<256, 64>(b, ctl, stream);
     return launch_igemm<128, 128>(b, ctl, stream);

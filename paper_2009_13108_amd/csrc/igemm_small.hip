@@ -26,43 +26,30 @@ constexpr int KB = 8;                 // 32-byte reduction steps per wave and lo
 constexpr int RP = 36;                // LDS row pitch of a partial tile (ints; 16-byte aligned)
 constexpr int MAX_M = 1024;           // eligibility: at most this many output rows
 
-// 16 bytes of a row at byte k, zero past L (rows may be only byte aligned).
-__device__ __forceinline__ v4i row_piece(const int8_t* row, int k, int L) {
-    v4i r = {0, 0, 0, 0};
-    if (k >= L) return r;
-    const int8_t* p = row + k;
-    const uintptr_t a = (uintptr_t)p;
-    if (k + 16 <= L) {
-        if ((a & 15) == 0) return *(const v4i*)p;
-        if ((a & 7) == 0) {
-            const int2 lo = *(const int2*)p, hi = *(const int2*)(p + 8);
-            r[0] = lo.x;
-            r[1] = lo.y;
-            r[2] = hi.x;
-            r[3] = hi.y;
-            return r;
-        }
-        if ((a & 3) == 0) {
-            const int* q = (const int*)p;
-            r[0] = q[0];
-            r[1] = q[1];
-            r[2] = q[2];
-            r[3] = q[3];
-            return r;
-        }
+// An operand's 16-byte piece is loaded from offset off, moved into the tensor
+// where it would pass the end, without a branch, so that all pieces of a batch
+// are in flight at once; piece_cut then zeroes what lies past L and, for the
+// moved ones, gathers the bytes singly.  Rows whose length is a multiple of 16
+// (WHOLE) need only the zeroing.  bytes >= 16.
+__device__ __forceinline__ v4i piece_load(const int8_t* base, uint32_t off, uint32_t bytes) {
+    return __builtin_bit_cast(v4i, load16_any(base + min(off, bytes - 16)));
+}
+template <bool WHOLE>
+__device__ __forceinline__ v4i piece_cut(v4i v, const int8_t* base, uint32_t off, uint32_t bytes, int k, int L) {
+    if (k >= L) return v4i{0, 0, 0, 0};
+    if (!WHOLE && (k + 16 > L || off + 16 > bytes)) {
+        if (off + 16 <= bytes) return __builtin_bit_cast(v4i, keep_bytes(__builtin_bit_cast(uint4, v), 0, L - k));
+        const int n = min(16, L - k);
+        uint32_t w[4] = {0u, 0u, 0u, 0u};
+        for (int i = 0; i < n; i++) w[i >> 2] |= (uint32_t)(uint8_t)base[off + i] << (8 * (i & 3));
+        return v4i{(int)w[0], (int)w[1], (int)w[2], (int)w[3]};
     }
-    const int n = min(16, L - k);
-    uint32_t w[4] = {0u, 0u, 0u, 0u};
-    for (int i = 0; i < n; i++) w[i >> 2] |= (uint32_t)(uint8_t)p[i] << (8 * (i & 3));
-    r[0] = (int)w[0];
-    r[1] = (int)w[1];
-    r[2] = (int)w[2];
-    r[3] = (int)w[3];
-    return r;
+    return v;
 }
 
 // One 32 x 32 tile: reduce, add the slices, then (threads < 256, four
 // consecutive channels of one row each) fold the maximum and store.
+template <bool WHOLE>
 __device__ __forceinline__ void small_tile(const IgemmProblem& P, int tile, int32_t* red, const RoundK& rk,
                                            int relu, bool do_store, bool do_max, uint32_t& tmax) {
     const int tiles_n = (P.Nout + 31) >> 5;
@@ -75,9 +62,10 @@ __device__ __forceinline__ void small_tile(const IgemmProblem& P, int tile, int3
     // Operand rows of this lane (clamped into the tensor; rows past the edge
     // load zeros).
     const bool nok = n0 + r32 < P.Nout, mok = m0 + r32 < P.M;
-    const int8_t* wrow = P.wgt + (int64_t)(nok ? n0 + r32 : 0) * L;
-    const int8_t* arow = P.act + (int64_t)(mok ? m0 + r32 : 0) * L;
+    const uint32_t wrow = (uint32_t)(nok ? n0 + r32 : 0) * (uint32_t)L;
+    const uint32_t arow = (uint32_t)(mok ? m0 + r32 : 0) * (uint32_t)L;
     const int Lw = nok ? L : 0, La = mok ? L : 0;
+    const uint32_t wbytes = (uint32_t)P.wgt_bytes, abytes = (uint32_t)P.act_bytes;
 
     v16i acc;
 #pragma unroll
@@ -88,8 +76,14 @@ __device__ __forceinline__ void small_tile(const IgemmProblem& P, int tile, int3
 #pragma unroll
         for (int j = 0; j < KB; j++) {
             const int k = (ks0 + j * SW) * 32 + kh;
-            a[j] = row_piece(wrow, k, Lw);
-            b[j] = row_piece(arow, k, La);
+            a[j] = piece_load(P.wgt, wrow + k, wbytes);
+            b[j] = piece_load(P.act, arow + k, abytes);
+        }
+#pragma unroll
+        for (int j = 0; j < KB; j++) {
+            const int k = (ks0 + j * SW) * 32 + kh;
+            a[j] = piece_cut<WHOLE>(a[j], P.wgt, wrow + k, wbytes, k, Lw);
+            b[j] = piece_cut<WHOLE>(b[j], P.act, arow + k, abytes, k, La);
         }
 #pragma unroll
         for (int j = 0; j < KB; j++) acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(a[j], b[j], acc, 0, 0, 0);
@@ -148,6 +142,7 @@ __device__ __forceinline__ void small_tile(const IgemmProblem& P, int tile, int3
 
 // Main launch: every tile once, the maximum folded in, the output rounded
 // with the shift of the previous call (none stored without a guess).
+template <bool WHOLE>
 __global__ __launch_bounds__(ST) void igemm_small_main(IgemmProblem P, IgemmCtl ctl) {
     __shared__ __attribute__((aligned(16))) int32_t red[SW * 32 * RP];
     __shared__ uint32_t wmax[ST / 64];
@@ -158,12 +153,13 @@ __global__ __launch_bounds__(ST) void igemm_small_main(IgemmProblem P, IgemmCtl 
     begin_call(st, slot, hint);
     const RoundK rk = make_round(hint < 0 ? 0 : hint, ctl.mode);
     uint32_t tmax = 0;
-    small_tile(P, blockIdx.x, red, rk, ctl.relu, hint >= 0, true, tmax);
+    small_tile<WHOLE>(P, blockIdx.x, red, rk, ctl.relu, hint >= 0, true, tmax);
     block_publish_max32(st, slot, tmax, wmax, snap);  // magnitudes <= 2^31
 }
 
 // Fix-up launch: with the final maximum, recompute every tile when the
 // guessed shift was wrong; workgroup 0 then finalizes the statistics.
+template <bool WHOLE>
 __global__ __launch_bounds__(ST) void igemm_small_fixup(IgemmProblem P, IgemmCtl ctl, int ntiles) {
     __shared__ __attribute__((aligned(16))) int32_t red[SW * 32 * RP];
     niti_stats* st = ctl.stats;
@@ -173,7 +169,7 @@ __global__ __launch_bounds__(ST) void igemm_small_fixup(IgemmProblem P, IgemmCtl
     if (bp != hint) {
         const RoundK rk = make_round(bp, ctl.mode);
         uint32_t dummy = 0;
-        for (int t = blockIdx.x; t < ntiles; t += gridDim.x) small_tile(P, t, red, rk, ctl.relu, true, false, dummy);
+        for (int t = blockIdx.x; t < ntiles; t += gridDim.x) small_tile<WHOLE>(P, t, red, rk, ctl.relu, true, false, dummy);
     }
     if (is_finisher()) finish_call(st, ctl.target, ctl.ex, ctl.static_flags, 1);
 }
@@ -191,21 +187,28 @@ bool igemm_small_eligible(const IgemmBatch& b) {
     if (p.H != p.OHc || p.W != p.OWc || p.st != 1 || p.off_h != 0 || p.off_w != 0) return false;
     if (p.OH != p.OHc || p.OW != p.OWc || p.os != 1 || p.oa != 0 || p.ob != 0) return false;
     if (p.ldo != p.Nout || p.zsib) return false;
+    if (p.L > 0 && (p.act_bytes < 16 || p.wgt_bytes < 16)) return false;   // pieces are loaded whole
     const int64_t tiles128 = (int64_t)((p.M + 127) / 128) * ((p.Nout + 127) / 128);
     return tiles128 < 64;
 }
 
-hipError_t igemm_small_run(IgemmBatch& b, IgemmCtl ctl, hipStream_t stream) {
-    const IgemmProblem& p = b.p[0];
+namespace {
+template <bool WHOLE>
+hipError_t launch_small(const IgemmProblem& p, const IgemmCtl& ctl, hipStream_t stream) {
     const int ntiles = ((p.M + 31) / 32) * ((p.Nout + 31) / 32);
     const int tk = timing_begin(NITI_TIMING_KERNEL, stream, "igemm_small_main");
-    hipLaunchKernelGGL(igemm_small_main, dim3(ntiles), dim3(ST), 0, stream, p, ctl);
+    hipLaunchKernelGGL(igemm_small_main<WHOLE>, dim3(ntiles), dim3(ST), 0, stream, p, ctl);
     timing_end(tk, stream);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     const int fix_grid = ntiles < kFixupGrid ? ntiles : kFixupGrid;
-    hipLaunchKernelGGL(igemm_small_fixup, dim3(fix_grid), dim3(ST), 0, stream, p, ctl, ntiles);
+    hipLaunchKernelGGL(igemm_small_fixup<WHOLE>, dim3(fix_grid), dim3(ST), 0, stream, p, ctl, ntiles);
     return hipGetLastError();
+}
+}  // namespace
+
+hipError_t igemm_small_run(IgemmBatch& b, IgemmCtl ctl, hipStream_t stream) {
+    return b.p[0].L % 16 == 0 ? launch_small<true>(b.p[0], ctl, stream) : launch_small<false>(b.p[0], ctl, stream);
 }
 
 }  // namespace niti

@@ -198,6 +198,29 @@ __device__ __forceinline__ uint32_t fdiv(uint32_t n, const FastDiv& f) {
 }
 
 // ---------------------------------------------------------------------------
+// 16 bytes from any address.  Global loads need no alignment on this target
+// (the compiler issues one 16-byte load), so rows at odd addresses cost one
+// load per piece and not one per byte.
+__device__ __forceinline__ uint4 load16_any(const void* p) {
+    uint4 v;
+    __builtin_memcpy(&v, p, 16);
+    return v;
+}
+
+// Bytes [lo, hi) of v, zero elsewhere (0 <= lo, hi <= 16).
+__device__ __forceinline__ uint4 keep_bytes(uint4 v, int lo, int hi) {
+    uint32_t w[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+    for (int q = 0; q < 4; q++) {
+        const int a = min(max(lo - 4 * q, 0), 4), b = min(max(hi - 4 * q, 0), 4);
+        const uint32_t from = a < 4 ? ~0u << (8 * a) : 0u;   // bytes a..3
+        const uint32_t below = b > 0 ? ~0u >> (8 * (4 - b)) : 0u;   // bytes 0..b-1
+        w[q] &= from & below;
+    }
+    return make_uint4(w[0], w[1], w[2], w[3]);
+}
+
+// ---------------------------------------------------------------------------
 __device__ __forceinline__ uint64_t wave_max_u64(uint64_t v) {
 #pragma unroll
     for (int o = 32; o >= 1; o >>= 1) {

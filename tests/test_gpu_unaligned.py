@@ -1,0 +1,74 @@
+"""The general implicit-GEMM kernel and the small-product kernel on rows that
+are only byte aligned: pieces that cross a row's end, a filter row's end, the
+image border and the tensor's first and last bytes; tile counts on both sides
+of the 64 x 64 rule; every rounding mode (stochastic rounding runs all its
+products there).  Exact against the oracle."""
+import pytest
+
+import oracle
+from paper_2009_13108_amd import inputs as I
+from paper_2009_13108_amd import niti
+from helpers import dev, host, krsc, nchw, nhwc, same_stats, say
+
+pytestmark = pytest.mark.gpu
+
+GEMMS = [
+    # M, N, K, relu, mode
+    (1, 1, 15, False, oracle.PSR), (3, 2, 17, True, oracle.PSR), (5, 33, 31, False, oracle.RTN),
+    (40, 70, 1111, True, oracle.PSR), (1025, 1029, 1, False, oracle.PSR), (1030, 64, 63, True, oracle.SR),
+    (1100, 1500, 1111, True, oracle.PSR), (1920, 2176, 65, False, oracle.PSR), (2049, 2040, 257, True, oracle.RTN),
+    (1111, 70, 321, False, oracle.SR), (2048, 2176, 127, False, oracle.SR),
+]
+
+
+@pytest.mark.parametrize("case", GEMMS)
+def test_products_of_unaligned_rows(case):
+    import torch
+    M, N, K, relu, mode = case
+    say("unaligned gemm", case)
+    A, B = I.weights(71, (M, K)), I.weights(72, (N, K))
+    C = torch.empty((M, N), dtype=torch.int8, device="cuda")
+    stats = niti.new_stats()
+    niti.set_sr_seed(stats, 3)
+    Ad, Bd = dev(A), dev(B)
+    for call in range(2):
+        exp, _, st = oracle.gemm_fwd(A, B, relu=relu, mode=mode, sr_seed=3, sr_call=call)
+        C.fill_(77)
+        niti.gemm_fwd(Ad, Bd, C, stats, relu=relu, mode=mode)
+        assert (host(C) == exp).all() and same_stats(niti.read_stats(stats)[0], st), call
+
+
+CONVS = [
+    # n, c, h, w, k, r, s, stride, pad, mode
+    (1, 4, 3, 3, 1, 3, 3, 1, 1, oracle.SR), (2, 20, 5, 7, 9, 3, 3, 1, 1, oracle.PSR),
+    (3, 36, 9, 8, 33, 5, 5, 2, 2, oracle.PSR), (2, 20, 7, 6, 130, 7, 7, 1, 3, oracle.RTN),
+    (2, 68, 6, 6, 66, 1, 1, 2, 0, oracle.PSR), (2, 64, 8, 9, 64, 3, 3, 1, 1, oracle.SR),
+    (1, 100, 5, 5, 10, 5, 3, 1, 2, oracle.SR), (9, 20, 60, 60, 200, 3, 3, 1, 1, oracle.PSR),
+]
+
+
+@pytest.mark.parametrize("case", CONVS)
+def test_convolutions_of_unaligned_rows(case):
+    import torch
+    n, c, h, w, k, r, s, stride, pad, mode = case
+    say("unaligned conv", case)
+    d = oracle.conv_desc(n, c, h, w, k, r, s, stride, pad)
+    gd = niti.ConvDesc.make(n, h, w, c, k, r, s, stride, pad)
+    P, Q = oracle.conv_out_hw(d)
+    x, wt, dy = I.weights(73, (n, c, h, w)), I.weights(74, (k, c, r, s)), I.errors8(75, (n, k, P, Q))
+    y = torch.empty(gd.y_shape(), dtype=torch.int8, device="cuda")
+    dx = torch.empty(gd.x_shape(), dtype=torch.int8, device="cuda")
+    stats = niti.new_stats(2)
+    niti.set_sr_seed(stats, 4)
+    ws = niti.new_workspace(max(niti.workspace_bytes(op, gd) for op in (niti.OP_CONV_FWD, niti.OP_CONV_BWD_DATA)))
+    xd, wd, dyd = dev(nhwc(x)), dev(krsc(wt)), dev(nhwc(dy))
+    for call in range(2):
+        y_exp, _, st_f = oracle.conv_fwd(d, x, wt, relu=True, mode=mode, sr_seed=4, sr_call=call)
+        dx_exp, _, st_b = oracle.conv_bwd_data(d, dy, wt, mode=mode, relu_src=x, sr_seed=4, sr_call=call)
+        y.fill_(77)
+        dx.fill_(77)
+        niti.conv_fwd(gd, xd, wd, y, stats, relu=True, mode=mode, stats_index=0, ws=ws)
+        niti.conv_bwd_data(gd, dyd, wd, dx, stats, ws, relu_src=xd, mode=mode, stats_index=1)
+        got = niti.read_stats(stats)
+        assert (nchw(host(y)) == y_exp).all() and same_stats(got[0], st_f), call
+        assert (nchw(host(dx)) == dx_exp).all() and same_stats(got[1], st_b), call
