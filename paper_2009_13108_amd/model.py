@@ -205,9 +205,8 @@ class IntNet:
                 nw -= 1
                 niti.stream_record(self.ev_bwd[nw], cur)
                 niti.stream_wait(self.sB, self.ev_bwd[nw])
-                with torch.cuda.stream(self.sB):
-                    niti.conv_bwd_weight(d, x_v, e_v, w_v, self.stats, self.ws_b, mu=mu, mode=self.grad_mode,
-                                         stats_index=L["stats"] + 2)
+                niti.conv_bwd_weight(d, x_v, e_v, w_v, self.stats, self.ws_b, mu=mu, mode=self.grad_mode,
+                                     stats_index=L["stats"] + 2, stream=self.sB)
             else:
                 niti.conv_bwd_weight(d, x_v, e_v, w_v, self.stats, self.ws, mu=mu, mode=self.grad_mode,
                                      stats_index=L["stats"] + 2)
