@@ -6,29 +6,35 @@
 // Load modes; all but kConv16 keep the per-step address work uniform:
 //   kGemm   plain matrix rows (H = W = 1, one tap): a lane's offset is fixed
 //           and the K step adds a uniform amount;
-//   kConv64 convolutions with C % 64 == 0: every 64-byte K step lies in one
-//           filter tap (r, s) and channel block c0, all uniform, so a lane
+//   kConv   convolutions whose channels are whole K steps: every step lies in
+//           one filter tap (r, s) and channel block c0, all uniform, so a lane
 //           only checks that its pixel's tap is inside the image;
 //   kWin    convolutions with few channels (S*C <= 64) over a zero-padded
 //           copy of the input: a filter row is one contiguous window of
 //           L = 16, 32 or 64 bytes (S pixels, zero weights past them), a K
-//           step covers 64/L filter rows, and every window is in bounds, so
+//           step covers KS/L filter rows, and every window is in bounds, so
 //           a lane's offset is fixed and the step adds a uniform amount;
 //   kConv16 convolutions with C % 16 == 0 that the others do not take (96
 //           channels, or more than 32 taps): each 16-byte piece lies in one
 //           filter tap, but the four pieces of a step may lie in different
 //           ones, so a lane carries its piece's (row, pixel, channel) and
-//           moves it by 64 bytes per step with two carries; ~18 vector
+//           moves it by a step with two carries; ~18 vector
 //           instructions per step.  Before, such layers ran on the general
 //           kernel: 5x5, 96 -> 256 channels at 27x27, batch 128: 156 -> 85 us.
 //
+// K steps are KS = 64 or 128 bytes per row.  Rows are hundreds of bytes apart,
+// and half of a 128-byte cache line costs the CU's load path as much as all
+// of it: a load-only probe of 16 KB steps took 0.19..0.25 us per CU in
+// 64-byte row segments (which is what a K step of the 128 x 128 tile took, not
+// its MFMAs) and 0.13 us in 128-byte ones.
+//
 // Loads.  Each wave instruction moves 64 lanes x 16 bytes into one 1 KiB LDS
-// block (lane l lands at block + 16 l); a block holds 16 operand rows of one
-// 64-byte K step.  A lane whose piece is outside the image, past the tensor
+// block (lane l lands at block + 16 l); a block holds 1024 / KS operand rows
+// of one K step.  A lane whose piece is outside the image, past the tensor
 // or past K uses an offset beyond the buffer's size, which the hardware
-// answers with zeros.  Within a row the four 16-byte chunks are stored
-// XOR-swizzled (position = chunk ^ f(row)) so the 32x32x32 MFMA fragment
-// reads (16 bytes per lane, 8 lanes per bank cycle) hit distinct banks.
+// answers with zeros.  Within a row the 16-byte chunks are stored
+// XOR-swizzled (position = chunk ^ f(row)) so that the 32x32x32 MFMA fragment
+// reads (16 bytes per lane, one chunk of 32 rows) hit distinct banks.
 //
 // Pipeline.  NS stages; stage k+NS-1 is issued while stage k is computed.
 // Loads past the last K step are issued anyway (as zeros), so the wait
@@ -39,16 +45,18 @@ namespace niti {
 
 namespace {
 
-constexpr int KSTEP = 64;  // K bytes per stage
 constexpr uint32_t kOOB = 0x80000000u;
 constexpr int kGemm = 0;
-constexpr int kConv64 = 1;
+constexpr int kConv = 1;
 constexpr int kWin = 2;
 constexpr int kConv16 = 3;
 
 typedef __attribute__((address_space(3))) void lds_void;
 
-__device__ __forceinline__ int swz(int row) { return ((row >> 1) ^ (row >> 2)) & 3; }
+template <int KS>
+__device__ __forceinline__ int swz(int row) {
+    return KS == 64 ? ((row >> 1) ^ (row >> 2)) & 3 : (row >> 1) & 7;
+}
 
 template <int N>
 __device__ __forceinline__ void wait_vm() {
@@ -63,21 +71,27 @@ __device__ __forceinline__ void wait_vm_lgkm0() {
     __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | 0x0070);
 }
 
-template <int BM, int BN, int NS, int WGM, int WGN>
+template <int BM, int BN, int NS, int WGM, int WGN, int KS>
 struct Cfg {
+    static constexpr int RPB = 1024 / KS;                   // rows per 1 KiB block
+    static constexpr int LPR = KS / 16;                     // lanes per row
+    static constexpr int NH = KS / 32;                      // MFMA depths per step
     static constexpr int NWAVES = WGM * WGN;
     static constexpr int NT = 64 * NWAVES;
     static constexpr int WTM = BM / WGM, WTN = BN / WGN;   // wave tile: pixels x channels
     static constexpr int FM = WTM / 32, FN = WTN / 32;
-    static constexpr int BLOCKS = (BM + BN) / 16;           // 1 KiB blocks per stage
-    static constexpr int ABLK = BN / 16;                    // blocks holding weight rows
+    static constexpr int BLOCKS = (BM + BN) / RPB;          // 1 KiB blocks per stage
+    static constexpr int ABLK = BN / RPB;                   // blocks holding weight rows
     // Weight blocks per wave: ABLK / NWAVES each, or (fewer blocks than
-    // waves) one each for waves 0 .. ABLK-1.
+    // waves) one each for waves 0 .. ABLK-1.  A wave takes every NWAVES-th
+    // block of an operand: the swizzle of 8-row blocks alternates with the
+    // block's parity, which a wave's blocks then share.
     static constexpr bool W_EVEN = ABLK % NWAVES == 0;
     static constexpr int IPW_W = W_EVEN ? ABLK / NWAVES : 1;
     static constexpr int IPW_A = (BLOCKS - ABLK) / NWAVES;  // activation blocks per wave
     static_assert((BLOCKS - ABLK) % NWAVES == 0 && (W_EVEN || ABLK < NWAVES), "load split over waves");
-    static constexpr int STAGE_BYTES = (BM + BN) * KSTEP;
+    static_assert(NWAVES % 2 == 0 && ABLK % 2 == 0, "one swizzle parity per wave");
+    static constexpr int STAGE_BYTES = (BM + BN) * KS;
     static constexpr int LDS_BYTES = NS * STAGE_BYTES;
     static constexpr int WGM_ = WGM, BN_ = BN;
     static_assert(BM * (BN + 16) <= LDS_BYTES, "output tile fits in the ring");
@@ -190,11 +204,11 @@ __device__ __forceinline__ void store_tile(const IgemmProblem& P, int tm, int tn
     }
 }
 
-template <int BM, int BN, int NS, int WGM, int WGN, int MODE>
+template <int BM, int BN, int NS, int WGM, int WGN, int KS, int MODE>
 __device__ __forceinline__ void dma_tile(const IgemmProblem& P, int tm, int tn, int8_t* lds, const RoundK& rk,
                                          int relu, int do_store, int do_max, uint64_t& tmax, niti_stats* snap_st,
                                          int snap_slot, uint64_t& snap) {
-    using T = Cfg<BM, BN, NS, WGM, WGN>;
+    using T = Cfg<BM, BN, NS, WGM, WGN, KS>;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int wm = wave % WGM, wn = wave / WGM;
@@ -205,22 +219,21 @@ __device__ __forceinline__ void dma_tile(const IgemmProblem& P, int tm, int tn, 
     // Per-lane row state for each load instruction: a wave issues IPW_W
     // weight blocks and IPW_A activation blocks per stage; wb / ab is the
     // lane's byte offset at K step 0 (kOOB for a row past the operand).
-    const int lrow = lane >> 2;
-    const uint32_t kpo = (uint32_t)(((lane & 3) ^ swz(lrow)) << 4);  // byte offset of this lane's chunk
+    const int lrow = lane / T::LPR;   // row within a block
+    const uint32_t kpo = (uint32_t)(((lane % T::LPR) ^ swz<KS>((wave & 1) * T::RPB + lrow)) << 4);  // byte offset of this lane's chunk
     uint32_t wb[T::IPW_W], ab[T::IPW_A];
-    // kConv64: taps (bit r*S+s) outside the image; kWin: filter row of the
+    // kConv: taps (bit r*S+s) outside the image; kWin: filter row of the
     // piece; kConv16: filter rows (low half) and columns (high half) inside
     uint32_t aux[T::IPW_A];
     const bool wload = T::W_EVEN || wave < T::ABLK;   // this wave loads weight blocks (uniform)
-    const int wblk0 = T::W_EVEN ? wave * T::IPW_W : wave;
 #pragma unroll
     for (int i = 0; i < T::IPW_W; i++) {
-        const int n = tn * BN + (wblk0 + i) * 16 + lrow;
+        const int n = tn * BN + (wave + i * T::NWAVES) * T::RPB + lrow;
         wb[i] = (wload && n < P.Nout) ? (uint32_t)n * (uint32_t)P.Ktot + kpo : kOOB;
     }
 #pragma unroll
     for (int i = 0; i < T::IPW_A; i++) {
-        const int m = tm * BM + (wave * T::IPW_A + i) * 16 + lrow;
+        const int m = tm * BM + (wave + i * T::NWAVES) * T::RPB + lrow;
         aux[i] = 0;
         if (MODE == kGemm) {
             ab[i] = m < P.M ? (uint32_t)m * (uint32_t)P.C + kpo : kOOB;
@@ -258,13 +271,13 @@ __device__ __forceinline__ void dma_tile(const IgemmProblem& P, int tm, int tn, 
         }
     }
 
-    const int nk = (P.Ktot + KSTEP - 1) / KSTEP;
+    const int nk = (P.Ktot + KS - 1) / KS;
     // Scalar instructions issue at about one per cycle per CU, shared by all
     // waves, so the load side keeps its per-step uniform work small: the
     // lanes' current offsets cvw / cva change only at events (a filter tap
     // change, the last K step, the end of K), counted down by ev; between
     // events a step adds to the two uniform offsets kb (weights, and kGemm
-    // activations) and sa (kConv64: channel offset within the tap; kWin:
+    // activations) and sa (kConv: channel offset within the tap; kWin:
     // window row offset).  The uniform part of an offset rides in the
     // instruction's SGPR offset; every lane offset that is not kOOB stays
     // inside its buffer together with it, and lanes whose piece is past K,
@@ -272,16 +285,17 @@ __device__ __forceinline__ void dma_tile(const IgemmProblem& P, int tm, int tn, 
     const uint32_t lds0 = lds_address(lds);
     uint32_t wdst[T::IPW_W], adst[T::IPW_A];   // this wave's blocks in stage 0
 #pragma unroll
-    for (int i = 0; i < T::IPW_W; i++) wdst[i] = __builtin_amdgcn_readfirstlane(lds0 + (uint32_t)(wblk0 + i) * 1024u);
+    for (int i = 0; i < T::IPW_W; i++) wdst[i] = __builtin_amdgcn_readfirstlane(lds0 + (uint32_t)(wave + i * T::NWAVES) * 1024u);
 #pragma unroll
     for (int i = 0; i < T::IPW_A; i++)
-        adst[i] = __builtin_amdgcn_readfirstlane(lds0 + (uint32_t)(T::ABLK + wave * T::IPW_A + i) * 1024u);
-    const int cbs = __builtin_amdgcn_readfirstlane(MODE == kConv64 ? P.C / KSTEP : 1);
+        adst[i] = __builtin_amdgcn_readfirstlane(lds0 + (uint32_t)(T::ABLK + wave + i * T::NWAVES) * 1024u);
+    const int cbs = __builtin_amdgcn_readfirstlane(MODE == kConv ? P.C / KS : 1);   // steps per tap
     const int ntap = __builtin_amdgcn_readfirstlane(P.R * P.S);
     const uint32_t da = __builtin_amdgcn_readfirstlane(
-        MODE == kWin ? (uint32_t)(KSTEP / P.L) * (uint32_t)(P.W * P.C) : (uint32_t)KSTEP);
+        MODE == kWin ? (uint32_t)(KS / P.L) * (uint32_t)(P.W * P.C) : (uint32_t)KS);
     const uint32_t klim = __builtin_amdgcn_readfirstlane(
-        MODE == kGemm ? (uint32_t)(P.Ktot - (nk - 1) * KSTEP) : (MODE == kWin ? (uint32_t)(P.R - (nk - 1) * (KSTEP / P.L)) : 0u));
+        MODE == kWin ? (uint32_t)(P.R - (nk - 1) * (KS / P.L)) : 0u);   // kWin: filter rows of the last step
+    const uint32_t kend = __builtin_amdgcn_readfirstlane((uint32_t)(P.Ktot - (nk - 1) * KS));   // its K bytes
     // kConv16: this lane's piece as filter row, pixel in it, channel, and its
     // offset from the pixel's first tap; a step of 64 bytes in those units.
     int pr = 0, ps = 0, pc = 0;
@@ -293,9 +307,9 @@ __device__ __forceinline__ void dma_tile(const IgemmProblem& P, int tm, int tn, 
         ps = ((int)kpo - pr * P.L) / P.C;
         pc = (int)kpo - pr * P.L - ps * P.C;
         poff = (uint32_t)((pr * P.W + ps) * P.C + pc);
-        step_r = KSTEP / P.L;
-        step_s = (KSTEP - step_r * P.L) / P.C;
-        step_c = KSTEP - step_r * P.L - step_s * P.C;
+        step_r = KS / P.L;
+        step_s = (KS - step_r * P.L) / P.C;
+        step_c = KS - step_r * P.L - step_s * P.C;
         step_off = (uint32_t)((step_r * P.W + step_s) * P.C + step_c);
         row_wrap = (uint32_t)((P.W - P.S) * P.C);
     }
@@ -313,16 +327,16 @@ __device__ __forceinline__ void dma_tile(const IgemmProblem& P, int tm, int tn, 
         ph = 1;
         ev = 1;
 #pragma unroll
-        for (int i = 0; i < T::IPW_W; i++) cvw[i] = (MODE == kGemm && kpo >= klim) ? kOOB : wb[i];
+        for (int i = 0; i < T::IPW_W; i++) cvw[i] = kpo >= kend ? kOOB : wb[i];
 #pragma unroll
-        for (int i = 0; i < T::IPW_A; i++) cva[i] = (MODE == kGemm ? kpo >= klim : aux[i] >= klim) ? kOOB : ab[i];
+        for (int i = 0; i < T::IPW_A; i++) cva[i] = (MODE == kGemm ? kpo >= kend : aux[i] >= klim) ? kOOB : ab[i];
     };
 #pragma unroll
     for (int i = 0; i < T::IPW_A; i++) cva[i] = ab[i];
     if (nk <= 0) {
         ph = 2;
         ev = 1 << 30;
-    } else if (MODE == kConv64) {
+    } else if (MODE == kConv) {
         set_tap();
         ev = cbs;
     } else {
@@ -331,7 +345,7 @@ __device__ __forceinline__ void dma_tile(const IgemmProblem& P, int tm, int tn, 
     }
     // Events are handled at the start of the issue that follows them.
     auto advance = [&]() {
-        if (MODE == kConv64 && tap + 1 < ntap) {
+        if (MODE == kConv && tap + 1 < ntap) {
             ++tap;
             if (++ts == P.S) {
                 ts = 0;
@@ -344,13 +358,16 @@ __device__ __forceinline__ void dma_tile(const IgemmProblem& P, int tm, int tn, 
             ev = cbs;
             return;
         }
-        if (MODE != kConv64 && ph == 0) {
+        if (MODE != kConv && ph == 0) {
             last_step();
             return;
         }
-        // Past the end of K the loads go on unchanged (the buffer bounds
-        // keep them harmless): they keep the wait counts constant, and the
-        // stages they fill are never multiplied.
+        // Past the end of K the loads go on as zeros: they keep the wait
+        // counts constant, and the stages they fill are never multiplied.
+#pragma unroll
+        for (int i = 0; i < T::IPW_W; i++) cvw[i] = kOOB;
+#pragma unroll
+        for (int i = 0; i < T::IPW_A; i++) cva[i] = kOOB;
         tap = 1 << 30;
         ph = 2;
         ev = 1 << 30;
@@ -370,7 +387,7 @@ __device__ __forceinline__ void dma_tile(const IgemmProblem& P, int tm, int tn, 
                 const uint32_t in = (aux[i] >> pr) & (aux[i] >> (16 + ps)) & 1u;
                 lds_dma16_at(act_rs, adst[i], slot, in && kin ? ab[i] + poff : kOOB, 0);
             }
-            kb += KSTEP;
+            kb += KS;
             pc += step_c;
             ps += step_s;
             pr += step_r;
@@ -393,7 +410,7 @@ __device__ __forceinline__ void dma_tile(const IgemmProblem& P, int tm, int tn, 
         }
 #pragma unroll
         for (int i = 0; i < T::IPW_A; i++) lds_dma16_at(act_rs, adst[i], slot, cva[i], MODE == kGemm ? kb : sa);
-        kb += KSTEP;
+        kb += KS;
         sa += da;
         ev = __builtin_amdgcn_readfirstlane(ev - 1);
     };
@@ -410,53 +427,56 @@ __device__ __forceinline__ void dma_tile(const IgemmProblem& P, int tm, int tn, 
 #pragma unroll
     for (int a = 0; a < T::FN; a++) {
         const int row = wn * T::WTN + a * 32 + (lane & 31);
-        a_off[a] = row * KSTEP;
-        a_sw[a] = swz(row & 15);
+        a_off[a] = row * KS;
+        a_sw[a] = swz<KS>(row & 15);
     }
 #pragma unroll
     for (int b = 0; b < T::FM; b++) {
         const int row = wm * T::WTM + b * 32 + (lane & 31);
-        b_off[b] = BN * KSTEP + row * KSTEP;
-        b_sw[b] = swz(row & 15);
+        b_off[b] = BN * KS + row * KS;
+        b_sw[b] = swz<KS>(row & 15);
     }
 
 #pragma unroll
     for (int s = 0; s < NS - 1; s++) issue(s);
 
-    // Register double buffer over the two 32-byte halves of a K step: the
-    // second half's fragments are read while the first half's MFMAs run, and
-    // the next stage's first half right after the barrier, before this
-    // stage's second-half MFMAs.  Before each barrier a wave waits for its
-    // own fragment reads (lgkmcnt 0), so once all waves pass it no read of
-    // the stage that the next load overwrites is still in flight.
-    auto read_half = [&](const int8_t* st, int ks, v4i (&fa)[T::FN], v4i (&fb)[T::FM]) {
+    // Register double buffer over the 32-byte depths of a K step: a depth's
+    // fragments are read while the previous one's MFMAs run, and the next
+    // stage's first right after the barrier, before this stage's last MFMAs.
+    // Before each barrier a wave waits for its own fragment reads (lgkmcnt 0),
+    // so once all waves pass it no read of the stage that the next load
+    // overwrites is still in flight.
+    v4i fa[2][T::FN], fb[2][T::FM];
+    auto read_depth = [&](const int8_t* st, int ks) {
         const int kp = (lane >> 5) + 2 * ks;
 #pragma unroll
-        for (int a = 0; a < T::FN; a++) fa[a] = *(const v4i*)(st + a_off[a] + ((kp ^ a_sw[a]) << 4));
+        for (int a = 0; a < T::FN; a++) fa[ks & 1][a] = *(const v4i*)(st + a_off[a] + ((kp ^ a_sw[a]) << 4));
 #pragma unroll
-        for (int b = 0; b < T::FM; b++) fb[b] = *(const v4i*)(st + b_off[b] + ((kp ^ b_sw[b]) << 4));
+        for (int b = 0; b < T::FM; b++) fb[ks & 1][b] = *(const v4i*)(st + b_off[b] + ((kp ^ b_sw[b]) << 4));
     };
-    auto mma_half = [&](const v4i (&fa)[T::FN], const v4i (&fb)[T::FM]) {
+    auto mma_depth = [&](int ks) {
 #pragma unroll
         for (int a = 0; a < T::FN; a++)
 #pragma unroll
             for (int b = 0; b < T::FM; b++)
-                acc[a][b] = __builtin_amdgcn_mfma_i32_32x32x32_i8(fa[a], fb[b], acc[a][b], 0, 0, 0);
+                acc[a][b] = __builtin_amdgcn_mfma_i32_32x32x32_i8(fa[ks & 1][a], fb[ks & 1][b], acc[a][b], 0, 0, 0);
     };
     // Loads per stage of this wave (uniform): the stage-exact wait counts.
     constexpr int LW = T::IPW_A + T::IPW_W, LA = T::IPW_A;
-    v4i fa0[T::FN], fb0[T::FM], fa1[T::FN], fb1[T::FM];
     if (wload)
         wait_vm<(NS - 2) * LW>();
     else
         wait_vm<(NS - 2) * LA>();
     __builtin_amdgcn_s_barrier();
-    read_half(lds, 0, fa0, fb0);
+    read_depth(lds, 0);
     for (int kt = 0; kt < nk; kt++) {
         const int8_t* st = lds + (kt % NS) * T::STAGE_BYTES;
         issue(kt + NS - 1);   // into the slot of stage kt - 1, which every wave has finished reading
-        read_half(st, 1, fa1, fb1);
-        mma_half(fa0, fb0);
+#pragma unroll
+        for (int ks = 0; ks + 1 < T::NH; ks++) {
+            read_depth(st, ks + 1);
+            mma_depth(ks);
+        }
         // (after the last step this reads a stage loaded past the end of K,
         // which no MFMA uses: it keeps the loop free of branches)
         if (wload)
@@ -464,8 +484,8 @@ __device__ __forceinline__ void dma_tile(const IgemmProblem& P, int tm, int tn, 
         else
             wait_vm_lgkm0<(NS - 2) * LA>();
         __builtin_amdgcn_s_barrier();
-        read_half(lds + ((kt + 1) % NS) * T::STAGE_BYTES, 0, fa0, fb0);
-        mma_half(fa1, fb1);
+        read_depth(lds + ((kt + 1) % NS) * T::STAGE_BYTES, 0);
+        mma_depth(T::NH - 1);
     }
     // Drain the loads issued past the end before the ring is reused.
     wait_vm<0>();
@@ -503,7 +523,7 @@ __device__ __forceinline__ void locate(const IgemmBatch& b, int t, int& prob, in
     tn = local - tm * b.p[p].tiles_n;
 }
 
-template <int BM, int BN, int NS, int WGM, int WGN, int MODE>
+template <int BM, int BN, int NS, int WGM, int WGN, int KS, int MODE>
 __global__ __launch_bounds__(64 * WGM * WGN, 1) void igemm_dma_main(IgemmBatch batch, IgemmCtl ctl) {
     extern __shared__ __attribute__((aligned(1024))) int8_t dyn_lds[];
     niti_stats* st = ctl.stats;
@@ -515,7 +535,7 @@ __global__ __launch_bounds__(64 * WGM * WGN, 1) void igemm_dma_main(IgemmBatch b
     locate(batch, blockIdx.x, prob, tm, tn);
     const RoundK rk = make_round(hint < 0 ? 0 : hint, ctl.mode);
     uint64_t tmax = 0;
-    dma_tile<BM, BN, NS, WGM, WGN, MODE>(batch.p[prob], tm, tn, dyn_lds, rk, ctl.relu, hint >= 0, 1, tmax, st, slot,
+    dma_tile<BM, BN, NS, WGM, WGN, KS, MODE>(batch.p[prob], tm, tn, dyn_lds, rk, ctl.relu, hint >= 0, 1, tmax, st, slot,
                                          snap);
     // Accumulator magnitudes are at most 2^31: 32-bit reductions are exact.
     // The ring is drained and the tile stored: its first bytes serve the
@@ -523,7 +543,7 @@ __global__ __launch_bounds__(64 * WGM * WGN, 1) void igemm_dma_main(IgemmBatch b
     block_publish_max32(st, slot, (uint32_t)tmax, (uint32_t*)dyn_lds, snap);
 }
 
-template <int BM, int BN, int NS, int WGM, int WGN, int MODE>
+template <int BM, int BN, int NS, int WGM, int WGN, int KS, int MODE>
 __global__ __launch_bounds__(64 * WGM * WGN, 1) void igemm_dma_fixup(IgemmBatch batch, IgemmCtl ctl) {
     extern __shared__ __attribute__((aligned(1024))) int8_t dyn_lds[];
     niti_stats* st = ctl.stats;
@@ -536,22 +556,22 @@ __global__ __launch_bounds__(64 * WGM * WGN, 1) void igemm_dma_fixup(IgemmBatch 
             int prob, tm, tn;
             locate(batch, t, prob, tm, tn);
             uint64_t dummy = 0, nosnap = 0;
-            dma_tile<BM, BN, NS, WGM, WGN, MODE>(batch.p[prob], tm, tn, dyn_lds, rk, ctl.relu, 1, 0, dummy, nullptr, 0,
+            dma_tile<BM, BN, NS, WGM, WGN, KS, MODE>(batch.p[prob], tm, tn, dyn_lds, rk, ctl.relu, 1, 0, dummy, nullptr, 0,
                                                  nosnap);
         }
     }
     if (is_finisher()) finish_call(st, ctl.target, ctl.ex, ctl.static_flags, 1);
 }
 
-template <int BM, int BN, int NS, int WGM, int WGN, int MODE>
+template <int BM, int BN, int NS, int WGM, int WGN, int KS, int MODE>
 hipError_t launch_dma(IgemmBatch& b, IgemmCtl ctl, hipStream_t stream) {
-    using T = Cfg<BM, BN, NS, WGM, WGN>;
+    using T = Cfg<BM, BN, NS, WGM, WGN, KS>;
     static bool attr_done = false;
     if (!attr_done) {
-        hipError_t e = hipFuncSetAttribute((const void*)igemm_dma_main<BM, BN, NS, WGM, WGN, MODE>,
+        hipError_t e = hipFuncSetAttribute((const void*)igemm_dma_main<BM, BN, NS, WGM, WGN, KS, MODE>,
                                            hipFuncAttributeMaxDynamicSharedMemorySize, T::LDS_BYTES);
         if (e != hipSuccess) return e;
-        e = hipFuncSetAttribute((const void*)igemm_dma_fixup<BM, BN, NS, WGM, WGN, MODE>,
+        e = hipFuncSetAttribute((const void*)igemm_dma_fixup<BM, BN, NS, WGM, WGN, KS, MODE>,
                                 hipFuncAttributeMaxDynamicSharedMemorySize, T::LDS_BYTES);
         if (e != hipSuccess) return e;
         attr_done = true;
@@ -566,16 +586,16 @@ hipError_t launch_dma(IgemmBatch& b, IgemmCtl ctl, hipStream_t stream) {
     }
     b.total_tiles = base;
     const int tk = timing_on() ? timing_begin(NITI_TIMING_KERNEL, stream,
-                                              kernel_label("igemm_dma_main<%d,%d,%d,%d,%d,%d>", BM, BN, NS, WGM,
-                                                           WGN, MODE))
+                                              kernel_label("igemm_dma_main<%d,%d,%d,%d,%d,%d,%d>", BM, BN, NS, WGM,
+                                                           WGN, KS, MODE))
                                : -1;
-    hipLaunchKernelGGL((igemm_dma_main<BM, BN, NS, WGM, WGN, MODE>), dim3(base), dim3(T::NT), T::LDS_BYTES, stream,
+    hipLaunchKernelGGL((igemm_dma_main<BM, BN, NS, WGM, WGN, KS, MODE>), dim3(base), dim3(T::NT), T::LDS_BYTES, stream,
                        b, ctl);
     timing_end(tk, stream);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     const int fix_grid = base < kFixupGrid ? base : kFixupGrid;
-    hipLaunchKernelGGL((igemm_dma_fixup<BM, BN, NS, WGM, WGN, MODE>), dim3(fix_grid), dim3(T::NT), T::LDS_BYTES,
+    hipLaunchKernelGGL((igemm_dma_fixup<BM, BN, NS, WGM, WGN, KS, MODE>), dim3(fix_grid), dim3(T::NT), T::LDS_BYTES,
                        stream, b, ctl);
     return hipGetLastError();
 }
@@ -583,17 +603,17 @@ hipError_t launch_dma(IgemmBatch& b, IgemmCtl ctl, hipStream_t stream) {
 int problem_mode(const IgemmProblem& p) {
     if (p.win) return kWin;
     if (p.H == 1 && p.W == 1 && p.R == 1 && p.off_h == 0 && p.off_w == 0 && p.L == p.C) return kGemm;
-    return p.C % KSTEP == 0 && p.R * p.S <= 32 ? kConv64 : kConv16;
+    return p.C % 64 == 0 && p.R * p.S <= 32 ? kConv : kConv16;
 }
 
 // The classes of a strided back-propagation share a launch and so a mode: a
-// class with too many taps for kConv64 takes the others along.
+// class with too many taps for kConv takes the others along.
 int batch_mode(const IgemmBatch& b) {
     int mode = problem_mode(b.p[0]);
     for (int i = 1; i < b.nprob; i++) {
         const int m = problem_mode(b.p[i]);
         if (m == mode) continue;
-        if ((m == kConv64 && mode == kConv16) || (m == kConv16 && mode == kConv64))
+        if ((m == kConv && mode == kConv16) || (m == kConv16 && mode == kConv))
             mode = kConv16;
         else
             return -1;
@@ -605,19 +625,42 @@ template <int MODE>
 hipError_t run_mode(IgemmBatch& b, IgemmCtl ctl, hipStream_t stream) {
     int64_t work = 0;
     int maxN = 0;
+    int64_t tiles128 = 0;
     for (int i = 0; i < b.nprob; i++) {
         work += (int64_t)b.p[i].M * b.p[i].Nout;
         maxN = b.p[i].Nout > maxN ? b.p[i].Nout : maxN;
+        tiles128 += (int64_t)((b.p[i].M + 127) / 128) * ((b.p[i].Nout + 127) / 128);
     }
-    // The largest tile that still gives most compute units a workgroup.
-    if (maxN <= 64) return launch_dma<256, 64, 4, 8, 1, MODE>(b, ctl, stream);
-    // 128 x 128 with eight 32 x 64 waves: two workgroups per CU (256 x 128
-    // fits one, by registers) and four waves per SIMD to hide each other's
-    // LDS and barrier waits.
-    if (maxN <= 128) return launch_dma<128, 128, 4, 4, 2, MODE>(b, ctl, stream);
-    if (work >= (int64_t)200 * 256 * 256) return launch_dma<256, 256, 3, 2, 4, MODE>(b, ctl, stream);
-    if (work >= (int64_t)200 * 256 * 128) return launch_dma<256, 128, 4, 2, 2, MODE>(b, ctl, stream);
-    return launch_dma<128, 128, 4, 4, 2, MODE>(b, ctl, stream);
+    // K steps of 128 bytes where a step is uniform (rows, or channels in whole
+    // 128s) and there is more than one 128 x 128 tile per CU; windows and
+    // carried pieces stay at 64.  Measured in us at 64 / 128: 14x14, 256
+    // channels, batch 128 (training pass) 104.0 / 97.7; 8192^3 421 / 404;
+    // 4096^3 63.3 / 61.3; but 7x7, 512 channels (196 tiles, one per CU and a
+    // deep ring either way) 97.1 / 97.1, 2048^3 18.8 / 19.5, and 5x5, 96
+    // channels (carried pieces) 272 / 287.
+    bool step128 = (MODE == kGemm || MODE == kConv) && tiles128 > 256;
+    for (int i = 0; i < b.nprob; i++) step128 = step128 && (MODE != kConv || b.p[i].C % 128 == 0);
+    // 256 x 256 tiles where they give most compute units a workgroup and pad
+    // the channels no further than 128 does (40 images of 56x56, 1x1,
+    // 320 -> 192, training pass: 149 us with 512 columns for 320, 132 with
+    // 384); 8192^3 480 us in tiles of 128, 402 in these.  Otherwise 128 x 128
+    // with eight 32 x 64 waves: two workgroups per CU and four waves per SIMD
+    // hide each other's LDS and barrier waits (256 x 128 tiles, one wave per
+    // SIMD, took the same or longer everywhere: 3000 x 3000 x 256 35.5 us
+    // against 25.6, 28x28 192 -> 160 training pass 157 against 126).
+    const bool big = work >= (int64_t)200 * 256 * 256 && (maxN + 255) / 256 * 256 <= (maxN + 127) / 128 * 128;
+    if constexpr (MODE == kGemm || MODE == kConv) {
+        if (step128) {
+            if (maxN <= 64) return launch_dma<256, 64, 2, 8, 1, 128, MODE>(b, ctl, stream);
+            if (maxN <= 128) return launch_dma<128, 128, 2, 4, 2, 128, MODE>(b, ctl, stream);
+            if (big) return launch_dma<256, 256, 2, 2, 4, 128, MODE>(b, ctl, stream);
+            return launch_dma<128, 128, 2, 4, 2, 128, MODE>(b, ctl, stream);
+        }
+    }
+    if (maxN <= 64) return launch_dma<256, 64, 4, 8, 1, 64, MODE>(b, ctl, stream);
+    if (maxN <= 128) return launch_dma<128, 128, 4, 4, 2, 64, MODE>(b, ctl, stream);
+    if (big) return launch_dma<256, 256, 3, 2, 4, 64, MODE>(b, ctl, stream);
+    return launch_dma<128, 128, 4, 4, 2, 64, MODE>(b, ctl, stream);
 }
 
 }  // namespace
@@ -635,7 +678,7 @@ bool igemm_dma_eligible(const IgemmBatch& b) {
         if (mode == kGemm) {
             if (p.C % 16 != 0 || p.Ktot != p.C) return false;
         } else if (mode == kWin) {
-            if ((p.L != 16 && p.L != 32 && p.L != 64) || p.Ktot != (p.R * p.L + KSTEP - 1) / KSTEP * KSTEP ||
+            if ((p.L != 16 && p.L != 32 && p.L != 64) || p.Ktot != (p.R * p.L + 63) / 64 * 64 ||
                 p.off_h != 0 || p.off_w != 0)
                 return false;
         } else {
@@ -653,7 +696,7 @@ hipError_t igemm_dma_run(IgemmBatch& b, IgemmCtl ctl, hipStream_t stream) {
         case kGemm: return run_mode<kGemm>(b, ctl, stream);
         case kWin: return run_mode<kWin>(b, ctl, stream);
         case kConv16: return run_mode<kConv16>(b, ctl, stream);
-        default: return run_mode<kConv64>(b, ctl, stream);
+        default: return run_mode<kConv>(b, ctl, stream);
     }
 }
 
