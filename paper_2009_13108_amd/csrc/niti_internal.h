@@ -139,7 +139,7 @@ hipError_t wgrad_small_run(WgradProblem& p, int8_t* w, int32_t* g32, int mu, int
 // 3x3 filters, C and K multiples of 64: all nine taps of a channel chunk per
 // workgroup (wgrad_tap.hip).
 bool wgrad_tap_eligible(const WgradProblem& p);
-WgradPlan wgrad_tap_plan(int64_t K, int64_t C, int64_t npix);
+WgradPlan wgrad_tap_plan(const WgradProblem& p);
 hipError_t wgrad_tap_run(WgradProblem& p, const WgradPlan& plan, hipStream_t stream);
 
 // Elementwise / reduction passes.

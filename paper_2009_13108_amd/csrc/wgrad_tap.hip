@@ -28,6 +28,25 @@
 // four input fragments feed as many MFMAs.  The two pixel halves' sums meet
 // in LDS at the end.
 //
+// Shared rows (SHARED: stride 1, padding 1, so that output and input pixels
+// have the same grid).  In the flattened pixel order the three taps of a
+// filter row read the same run of input pixels, shifted by one: output pixel p
+// and tap (r, s) meet input pixel p + (r-1) W + (s-1).  A stage then holds three
+// runs of 130 pixels instead of nine of 128, a third of the load traffic, and
+// the loads were what bounded the kernel: 32-byte row pieces cost the load
+// path as much as whole cache lines.  Runs are loaded with the pixels of rows
+// that tap row r must not see as zeros (the position within the image decides:
+// the last row for r = 0, the first for r = 2; they are the rows of the
+// neighbouring image in the flattened order).  Across the left and right
+// borders the shifted runs read the neighbouring row's end, so the error
+// fragments of the taps s = 0 and s = 2 are masked at the pixels of the first
+// and the last column; the loaders write those byte masks beside the stage.
+// Training passes at batch 128: 28x28, 128 channels 99.4 -> 94.7 us; 14x14, 256
+// channels 93.6 -> 89.5; 7x7, 512 channels 92.7 -> 91.0; a VGG-small-7 step at
+// batch 256 999 -> 946 us.  With 64 channels two pixels share a cache line and
+// the nine runs cost less than the masks (56x56: 102.2 against 103.4 us), so
+// those layers keep them.
+//
 // Issue cost.  Every instruction a wave issues besides its MFMAs holds the
 // SIMD's MFMA pipe for a few cycles (about three and a half with one wave
 // per SIMD, about two with two waves), so the kernel keeps the instruction
@@ -52,6 +71,13 @@ constexpr int XREG = PIX * CW;            // bytes of one [128 pixels][32 bytes]
 constexpr int DOFF = NTAP * XREG;         // dy region [128 pixels][64 bytes]
 constexpr int STAGE = DOFF + PIX * 64;
 constexpr int LOADS = NTAP + 2;           // loads per wave and stage
+// Shared rows: three runs of 160 pixels (130 used), a block of slack so that
+// every loader wave has the same count, the dy region, two byte masks.
+constexpr int RUN = 160 * CW;
+constexpr int S_DOFF = 16 * 1024;
+constexpr int S_MOFF = S_DOFF + PIX * 64;
+constexpr int S_STAGE = S_MOFF + 1024;
+constexpr int S_LOADS = 4 + 2;
 constexpr uint32_t kOOB = 0x80000000u;
 
 typedef __attribute__((address_space(3))) v2i lds_v2i;
@@ -125,6 +151,46 @@ struct TapHalf {
     static constexpr int N = TH ? 4 : 5;    // taps
 };
 constexpr int NTHREADS = 512;
+
+// Both pixel halves' sums to the partial tile.
+template <int TH>
+__device__ __forceinline__ void tap_finish(const WgradProblem& P, int8_t* lds, int split, int c0, int k0, int wk, int ph,
+                                           int lane, v16i (&acc)[TapHalf<TH>::N]) {
+    constexpr int T0 = TapHalf<TH>::T0, NTW = TapHalf<TH>::N;
+    // The two pixel halves: wave (wk, 1, TH) hands its sums to wave
+    // (wk, 0, TH) through LDS, slot [wk][tap][jj][lane] of 16 bytes, which
+    // adds them to its own and stores.
+    v4i* xch = (v4i*)lds;
+    if (ph == 1) {
+#pragma unroll
+        for (int t = 0; t < NTW; t++)
+#pragma unroll
+            for (int jj = 0; jj < 4; jj++) {
+                v4i q;
+                q[0] = acc[t][4 * jj];
+                q[1] = acc[t][4 * jj + 1];
+                q[2] = acc[t][4 * jj + 2];
+                q[3] = acc[t][4 * jj + 3];
+                xch[((wk * NTAP + T0 + t) * 4 + jj) * 64 + lane] = q;
+            }
+    }
+    __syncthreads();
+    if (ph == 1) return;
+
+    // acc[t] element 4*jj + i: channel c0 + 8*jj + 4*(lane/32) + i of tap
+    // T0 + t, output channel k0 + 32*wk + lane%32: four consecutive columns
+    // per store.
+    int32_t* out = P.part + (int64_t)split * P.K * P.ncol + (int64_t)(k0 + 32 * wk + (lane & 31)) * P.ncol;
+#pragma unroll
+    for (int t = 0; t < NTW; t++)
+#pragma unroll
+        for (int jj = 0; jj < 4; jj++) {
+            const v4i o = xch[((wk * NTAP + T0 + t) * 4 + jj) * 64 + lane];
+            const int col = (T0 + t) * P.C + c0 + 8 * jj + 4 * (lane >> 5);
+            *(int4*)(out + col) = make_int4(acc[t][4 * jj] + o[0], acc[t][4 * jj + 1] + o[1],
+                                            acc[t][4 * jj + 2] + o[2], acc[t][4 * jj + 3] + o[3]);
+        }
+}
 
 template <int NS, int TH>
 __device__ __forceinline__ void tap_body(const WgradProblem& P, int8_t* lds, int split, int c0, int k0, int pbeg,
@@ -285,45 +351,162 @@ __device__ __forceinline__ void tap_body(const WgradProblem& P, int8_t* lds, int
     wait_lds0();
     __syncthreads();   // the ring is free
 
-    // The two pixel halves: wave (wk, 1, TH) hands its sums to wave
-    // (wk, 0, TH) through LDS, slot [wk][tap][jj][lane] of 16 bytes, which
-    // adds them to its own and stores.
-    v4i* xch = (v4i*)lds;
-    if (ph == 1) {
-#pragma unroll
-        for (int t = 0; t < NTW; t++)
-#pragma unroll
-            for (int jj = 0; jj < 4; jj++) {
-                v4i q;
-                q[0] = acc[t][4 * jj];
-                q[1] = acc[t][4 * jj + 1];
-                q[2] = acc[t][4 * jj + 2];
-                q[3] = acc[t][4 * jj + 3];
-                xch[((wk * NTAP + T0 + t) * 4 + jj) * 64 + lane] = q;
-            }
-    }
-    __syncthreads();
-    if (ph == 1) return;
+    tap_finish<TH>(P, lds, split, c0, k0, wk, ph, lane, acc);
+}
 
-    // acc[t] element 4*jj + i: channel c0 + 8*jj + 4*(lane/32) + i of tap
-    // T0 + t, output channel k0 + 32*wk + lane%32: four consecutive columns
-    // per store.
-    int32_t* out = P.part + (int64_t)split * P.K * P.ncol + (int64_t)(k0 + 32 * wk + (lane & 31)) * P.ncol;
+// The same for shared rows (see the head of the file); the pixel halves, the
+// taps of a wave, the exchange and the stores are those of tap_body.
+template <int NS, int TH>
+__device__ __forceinline__ void tap_body_shared(const WgradProblem& P, int8_t* lds, int split, int c0, int k0, int pbeg,
+                                                int nsteps) {
+    constexpr int T0 = TapHalf<TH>::T0, NTW = TapHalf<TH>::N;
+    constexpr bool LOADER = TH == 0;
+    constexpr int NR = 2 * (NTW + 3);      // fragment and mask reads per stage
+    constexpr int NM = 2 * NTW;            // MFMAs per stage
+    constexpr int NG = LOADER ? S_LOADS : NTW;   // issue groups per step
+    const int lane = threadIdx.x & 63;
+    const int sub = __builtin_amdgcn_readfirstlane((threadIdx.x >> 6) & 3);
+    const int wk = sub & 1, ph = sub >> 1;
+
+    const u32x4 xrs = raw_rsrc(P.x, (uint32_t)P.x_bytes);
+    const u32x4 drs = raw_rsrc(P.dy, (uint32_t)P.dy_bytes);
+    const uint32_t lds0 = lds_address(lds);
+
+    // Loader wave sub fills x blocks sub, sub + 4, sub + 8, sub + 12 (block b:
+    // pixels 32 (b % 5) .. of run b / 5; block 15 is the slack) and dy blocks
+    // 2 sub, 2 sub + 1, and writes the masks of pixels 32 sub .. +31.  Offsets,
+    // positions in the image and columns move by a stage with adds.  Offsets
+    // before the first image and past the last lie outside the buffer.
+    const uint32_t hw = (uint32_t)(P.H * P.W);
+    const uint32_t rem_step = PIX % hw, col_step = PIX % (uint32_t)P.Q;
+    uint32_t xo[4], rem[4], lo[4], len[4], dofs[2], col = 0;
+    if (LOADER) {
+#pragma unroll
+        for (int i = 0; i < 4; i++) {
+            const int b = sub + 4 * i, r = b / 5, j = (b % 5) * 32 + (lane >> 1);
+            const int q = pbeg + (r - 1) * P.W - 1 + j;
+            const uint32_t qq = (uint32_t)(q + 2 * (int)hw);   // not negative: q >= -(W + 1)
+            rem[i] = qq - fdiv(qq, P.div_pq) * hw;
+            xo[i] = (uint32_t)q * (uint32_t)P.C + (uint32_t)c0 + (uint32_t)((lane & 1) << 4);
+            lo[i] = r == 2 ? (uint32_t)P.W : 0u;
+            len[i] = b >= 15 ? 0u : (r == 1 ? hw : hw - (uint32_t)P.W);
+        }
+#pragma unroll
+        for (int u = 0; u < 2; u++) {
+            const int drow = 32 * sub + 16 * u + (lane >> 2);
+            dofs[u] = (uint32_t)(pbeg + drow) * (uint32_t)P.K + (uint32_t)k0 +
+                      (uint32_t)(((lane & 3) ^ swz(drow)) << 4);
+        }
+        const uint32_t pm = (uint32_t)(pbeg + 32 * sub + (lane & 31));
+        col = pm - fdiv(pm, P.div_q) * (uint32_t)P.Q;
+    }
+    const uint32_t bad_col = lane < 32 ? 0u : (uint32_t)P.Q - 1u;   // column without tap s = 0 / s = 2
+    int8_t* mdst = lds + S_MOFF + (lane >> 5) * PIX + 32 * sub + (lane & 31);
+    int next = 0;
+    // Load g of the next stage: four x blocks, two dy blocks (and the masks).
+    auto load = [&](int g) {
+        const uint32_t st = lds0 + (uint32_t)((next % NS) * S_STAGE);
+        if (g < 4) {
+            const uint32_t v = rem[g] - lo[g] < len[g] ? xo[g] : kOOB;
+            lds_dma16_at(xrs, st, (uint32_t)((sub + 4 * g) * 1024), v, 0);
+            xo[g] += (uint32_t)(PIX * P.C);
+            rem[g] += rem_step;
+            rem[g] -= rem[g] >= hw ? hw : 0u;
+        } else {
+            const int u = g - 4;
+            lds_dma16_at(drs, st, (uint32_t)(S_DOFF + (2 * sub + u) * 1024), dofs[u], 0);
+            dofs[u] += (uint32_t)(PIX * P.K);
+            if (u == 1) {
+                mdst[(next % NS) * S_STAGE] = col == bad_col ? 0 : -1;
+                col += col_step;
+                col -= col >= (uint32_t)P.Q ? (uint32_t)P.Q : 0u;
+                next++;
+            }
+        }
+    };
+
+    const FragOff fo_x[2] = {frag_off32(64 * ph, lane), frag_off32(64 * ph + 32, lane)};
+    const FragOff fo_d[2] = {frag_off64(64 * ph, 32 * wk, lane), frag_off64(64 * ph + 32, 32 * wk, lane)};
+    const int mo = 64 * ph + 16 * (lane >> 5);
+
+    v16i acc[NTW];
 #pragma unroll
     for (int t = 0; t < NTW; t++)
 #pragma unroll
-        for (int jj = 0; jj < 4; jj++) {
-            const v4i o = xch[((wk * NTAP + T0 + t) * 4 + jj) * 64 + lane];
-            const int col = (T0 + t) * P.C + c0 + 8 * jj + 4 * (lane >> 5);
-            *(int4*)(out + col) = make_int4(acc[t][4 * jj] + o[0], acc[t][4 * jj + 1] + o[1],
-                                            acc[t][4 * jj + 2] + o[2], acc[t][4 * jj + 3] + o[3]);
+        for (int e = 0; e < 16; e++) acc[t][e] = 0;
+
+    struct Frags {
+        v4i d[2], m[2][2];   // error, its masks for s = 0 and s = 2
+        v4i x[2][NTW];
+    };
+    auto read_one = [&](int slot, int f, Frags& F) {
+        const uint32_t st = lds0 + (uint32_t)(slot * S_STAGE);
+        const int ks = f / (NTW + 3), i = f % (NTW + 3);
+        if (i == 0)
+            F.d[ks] = tr_frag(st + fo_d[ks].lo, st + fo_d[ks].hi, S_DOFF);
+        else if (i < 3)
+            F.m[ks][i - 1] = *(const v4i*)(lds + slot * S_STAGE + S_MOFF + (i - 1) * PIX + 32 * ks + mo);
+        else
+            F.x[ks][i - 3] = tr_frag(st + fo_x[ks].lo, st + fo_x[ks].hi,
+                                     ((T0 + i - 3) / 3) * RUN + ((T0 + i - 3) % 3) * CW);
+    };
+    // Step: as in tap_body.
+    auto step = [&](int it, Frags& cur, Frags& nxt) {
+        if (LOADER) wait_vm<(NS - 2) * S_LOADS>();
+        wait_lds0();
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");   // the mask reads below follow the barrier
+        const int slot1 = (it + 1) % NS;
+#pragma unroll
+        for (int ks = 0; ks < 2; ks++) {
+            cur.m[ks][0] &= cur.d[ks];
+            cur.m[ks][1] &= cur.d[ks];
         }
+#pragma unroll
+        for (int g = 0; g < NG; g++) {
+            if (LOADER) load(g);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int f = (g * NR) / NG; f < ((g + 1) * NR) / NG; f++) read_one(slot1, f, nxt);
+#pragma unroll
+            for (int m = (g * NM) / NG; m < ((g + 1) * NM) / NG; m++) {
+                const int ks = m / NTW, t = m % NTW, sft = (T0 + t) % 3;
+                acc[t] = __builtin_amdgcn_mfma_i32_32x32x32_i8(
+                    cur.x[ks][t], sft == 0 ? cur.m[ks][0] : (sft == 1 ? cur.d[ks] : cur.m[ks][1]), acc[t], 0, 0, 0);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    };
+
+    if (LOADER) {
+#pragma unroll
+        for (int s = 0; s < NS; s++)
+#pragma unroll
+            for (int g = 0; g < S_LOADS; g++) load(g);
+        wait_vm<(NS - 1) * S_LOADS>();
+        wait_lds0();
+    }
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    Frags f0, f1;
+#pragma unroll
+    for (int f = 0; f < NR; f++) read_one(0, f, f0);
+    int it = 0;
+    for (; it + 1 < nsteps; it += 2) {
+        step(it, f0, f1);
+        step(it + 1, f1, f0);
+    }
+    if (it < nsteps) step(it, f0, f1);
+    wait_vm<0>();
+    wait_lds0();
+    __syncthreads();   // the ring is free
+    tap_finish<TH>(P, lds, split, c0, k0, wk, ph, lane, acc);
 }
 
 // Work items (split, tile), tile fastest, cut into eight equal consecutive
 // runs, one per XCD (workgroup L runs on XCD L % 8), so the tiles of one pixel
 // range share an XCD and its L2.
-template <int NS>
+template <int NS, bool SHARED>
 __global__ __launch_bounds__(NTHREADS, 1) void wgrad_tap_kernel(WgradProblem P, int tiles_c, int tiles_k, int splits) {
     extern __shared__ __attribute__((aligned(1024))) int8_t lds[];
     const int ntiles = tiles_c * tiles_k;
@@ -337,6 +520,13 @@ __global__ __launch_bounds__(NTHREADS, 1) void wgrad_tap_kernel(WgradProblem P, 
     const int pbeg = split * P.chunk;
     const int pend = min(P.npix, pbeg + P.chunk);
     const int nsteps = pend > pbeg ? (pend - pbeg + PIX - 1) / PIX : 0;
+    if constexpr (SHARED) {
+        if (__builtin_amdgcn_readfirstlane(threadIdx.x >> 8) == 0)
+            tap_body_shared<NS, 0>(P, lds, split, c0, k0, pbeg, nsteps);
+        else
+            tap_body_shared<NS, 1>(P, lds, split, c0, k0, pbeg, nsteps);
+        return;
+    }
     if (__builtin_amdgcn_readfirstlane(threadIdx.x >> 8) == 0)
         tap_body<NS, 0>(P, lds, split, c0, k0, pbeg, pend, nsteps);
     else
@@ -350,17 +540,35 @@ bool wgrad_tap_eligible(const WgradProblem& p) {
            p.x_bytes < ((int64_t)1 << 31) && p.dy_bytes > 0 && p.dy_bytes < ((int64_t)1 << 31);
 }
 
-WgradPlan wgrad_tap_plan(int64_t K, int64_t C, int64_t npix) {
+namespace {
+
+// Output and input pixels on one grid (stride 1, padding 1), and room in the
+// 32-bit offsets for the stages that the ring loads past the last pixel.
+bool shared_rows(const WgradProblem& p) {
+    const int64_t over = 8 * PIX + 2 * (int64_t)p.W + 2;
+    return p.C >= 128 && p.sh == 1 && p.sw == 1 && p.ph == 1 && p.pw == 1 && p.H == p.P && p.W == p.Q &&
+           p.x_bytes + over * p.C < ((int64_t)1 << 31) && p.dy_bytes + over * p.K < ((int64_t)1 << 31) &&
+           (int64_t)p.npix + over + 2 * (int64_t)p.H * p.W < ((int64_t)1 << 31);
+}
+
+}  // namespace
+
+WgradPlan wgrad_tap_plan(const WgradProblem& p) {
+    const int64_t K = p.K, C = p.C, npix = p.npix;
     WgradPlan pl;
     pl.tbk = 64;
     const int64_t tiles = (K / 64) * (C / CW);
     const int64_t steps = (npix + PIX - 1) / PIX;
-    // About 192 workgroups, at least two stages each.  A workgroup holds
-    // most of its CU's LDS and registers, so a grid of one per CU would shut
-    // out a kernel running beside it on another stream (the back-propagation
-    // of a training step); leaving a quarter of the CUs free measured ~2%
-    // faster steps than 256, 160, 224 or a floor of 192 / tiles.
-    int64_t splits = (192 + tiles - 1) / tiles;
+    // Workgroups to aim for, at least two stages each.  A workgroup holds most
+    // of its CU's LDS and registers, so a grid of one per CU shuts out a
+    // kernel running beside it on another stream (the back-propagation of a
+    // training step).  Shared rows leave a quarter of the CUs free: one per CU
+    // gained 1% in a layer alone and lost 1 to 2% in two-stream steps.  The
+    // nine-run form is slower, and idle CUs cost it more: the strided 28x28,
+    // 128 -> 256 layer's training pass took 89.2 us at 192 and 83.8 at 256,
+    // and a ResNet-18 layer-set step on two streams 1.685 and 1.679 ms.
+    const int64_t groups = shared_rows(p) ? 192 : 256;
+    int64_t splits = (groups + tiles - 1) / tiles;
     const int64_t max_splits = steps / 2 > 1 ? steps / 2 : 1;
     if (splits > max_splits) splits = max_splits;
     if (splits < 1) splits = 1;
@@ -371,24 +579,35 @@ WgradPlan wgrad_tap_plan(int64_t K, int64_t C, int64_t npix) {
     return pl;
 }
 
-hipError_t wgrad_tap_run(WgradProblem& p, const WgradPlan& plan, hipStream_t stream) {
-    constexpr int NS = 3;
-    constexpr int LDS = NS * STAGE;
-    static_assert(LDS >= 2 * NTAP * 4 * 64 * 16, "exchange area");
+namespace {
+
+template <int NS, bool SHARED>
+hipError_t launch_tap(const WgradProblem& p, const WgradPlan& plan, hipStream_t stream) {
+    constexpr int LDS = NS * (SHARED ? S_STAGE : STAGE);
+    static_assert(LDS >= 2 * NTAP * 4 * 64 * 16 && LDS <= 160 * 1024, "exchange area");
     static bool attr_done = false;
     if (!attr_done) {
-        hipError_t e = hipFuncSetAttribute((const void*)wgrad_tap_kernel<NS>,
+        hipError_t e = hipFuncSetAttribute((const void*)wgrad_tap_kernel<NS, SHARED>,
                                            hipFuncAttributeMaxDynamicSharedMemorySize, LDS);
         if (e != hipSuccess) return e;
         attr_done = true;
     }
-    p.chunk = plan.chunk;
     const int tc = p.C / CW, tk = p.K / 64;
     const int64_t grid = (int64_t)8 * (((int64_t)tc * tk * plan.splits + 7) / 8);
-    const int t = timing_on() ? timing_begin(NITI_TIMING_KERNEL, stream, kernel_label("wgrad_tap_kernel<%d>", NS)) : -1;
-    hipLaunchKernelGGL((wgrad_tap_kernel<NS>), dim3((unsigned)grid), dim3(NTHREADS), LDS, stream, p, tc, tk, plan.splits);
+    const int t = timing_on() ? timing_begin(NITI_TIMING_KERNEL, stream,
+                                             kernel_label("wgrad_tap_kernel<%d,%d>", NS, (int)SHARED))
+                              : -1;
+    hipLaunchKernelGGL((wgrad_tap_kernel<NS, SHARED>), dim3((unsigned)grid), dim3(NTHREADS), LDS, stream, p, tc, tk,
+                       plan.splits);
     timing_end(t, stream);
     return hipGetLastError();
+}
+
+}  // namespace
+
+hipError_t wgrad_tap_run(WgradProblem& p, const WgradPlan& plan, hipStream_t stream) {
+    p.chunk = plan.chunk;
+    return shared_rows(p) ? launch_tap<5, true>(p, plan, stream) : launch_tap<3, false>(p, plan, stream);
 }
 
 }  // namespace niti
