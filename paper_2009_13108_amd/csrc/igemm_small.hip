@@ -6,11 +6,14 @@
 //
 // With so few outputs a tiled kernel runs on a handful of CUs and each of
 // them walks the reduction step by step, paying a memory round trip per
-// step.  Here a workgroup owns one 32 x 32 output tile and its eight waves
-// take interleaved 32-byte slices of the reduction: every wave issues all
-// of its operand loads at once (straight into MFMA operand registers, no
-// LDS staging), runs its MFMAs, and the eight partial tiles are added in
-// LDS.  The epilogue (optional ReLU, tensor maximum, shift-and-round,
+// step.  Here a workgroup owns one output tile of 32 channels and 32 or 64
+// rows and its eight waves take interleaved 64-byte slices of the reduction:
+// every wave issues all of its operand loads at once (straight into MFMA
+// operand registers, no LDS staging), runs its MFMAs, and the eight partial
+// tiles are added in LDS.  The 16 x 16 x 64 MFMA makes a load instruction read
+// 64 consecutive bytes of 16 rows; the 32 x 32 x 32 one read 32 of 32 rows, and
+// rows are far apart, so that each instruction touched twice as many cache
+// lines for the same data.  The epilogue (optional ReLU, tensor maximum, shift-and-round,
 // backward ReLU mask) and the exponent handling (rounding with the previous
 // call's shift, then a fix-up launch that recomputes on a miss) are those of
 // the other implicit-GEMM kernels.
@@ -22,7 +25,7 @@ namespace {
 
 constexpr int SW = 8;                 // waves per workgroup (reduction slices)
 constexpr int ST = SW * 64;           // threads per workgroup
-constexpr int KB = 8;                 // 32-byte reduction steps per wave and load batch
+constexpr int KB = 4;                 // 64-byte reduction steps per wave and load batch
 constexpr int RP = 36;                // LDS row pitch of a partial tile (ints; 16-byte aligned)
 constexpr int MAX_M = 1024;           // eligibility: at most this many output rows
 
@@ -47,66 +50,83 @@ __device__ __forceinline__ v4i piece_cut(v4i v, const int8_t* base, uint32_t off
     return v;
 }
 
-// One 32 x 32 tile: reduce, add the slices, then (threads < 256, four
-// consecutive channels of one row each) fold the maximum and store.
-template <bool WHOLE>
+// One tile of 16 FM rows x 32 channels: reduce, add the slices, then (four
+// consecutive channels of one row per thread) fold the maximum and store.
+template <bool WHOLE, int FM>
 __device__ __forceinline__ void small_tile(const IgemmProblem& P, int tile, int32_t* red, const RoundK& rk,
                                            int relu, bool do_store, bool do_max, uint32_t& tmax) {
+    constexpr int FN = 2, ROWS = 16 * FM;
     const int tiles_n = (P.Nout + 31) >> 5;
     const int tm = tile / tiles_n, tn = tile - tm * tiles_n;
-    const int m0 = tm * 32, n0 = tn * 32;
+    const int m0 = tm * ROWS, n0 = tn * 32;
     const int lane = threadIdx.x & 63;
     const int wave = threadIdx.x >> 6;
-    const int r32 = lane & 31, kh = (lane >> 5) * 16;
+    const int r16 = lane & 15, kh = (lane >> 4) * 16;
     const int L = P.L;
     // Operand rows of this lane (clamped into the tensor; rows past the edge
     // load zeros).
-    const bool nok = n0 + r32 < P.Nout, mok = m0 + r32 < P.M;
-    const uint32_t wrow = (uint32_t)(nok ? n0 + r32 : 0) * (uint32_t)L;
-    const uint32_t arow = (uint32_t)(mok ? m0 + r32 : 0) * (uint32_t)L;
-    const int Lw = nok ? L : 0, La = mok ? L : 0;
+    uint32_t wrow[FN], arow[FM];
+    int Lw[FN], La[FM];
+#pragma unroll
+    for (int f = 0; f < FN; f++) {
+        const int n = n0 + 16 * f + r16;
+        wrow[f] = (uint32_t)(n < P.Nout ? n : 0) * (uint32_t)L;
+        Lw[f] = n < P.Nout ? L : 0;
+    }
+#pragma unroll
+    for (int f = 0; f < FM; f++) {
+        const int m = m0 + 16 * f + r16;
+        arow[f] = (uint32_t)(m < P.M ? m : 0) * (uint32_t)L;
+        La[f] = m < P.M ? L : 0;
+    }
     const uint32_t wbytes = (uint32_t)P.wgt_bytes, abytes = (uint32_t)P.act_bytes;
 
-    v16i acc;
+    v4i acc[FN][FM];
 #pragma unroll
-    for (int e = 0; e < 16; e++) acc[e] = 0;
-    const int nks = (L + 31) >> 5;
+    for (int a = 0; a < FN; a++)
+#pragma unroll
+        for (int b = 0; b < FM; b++) acc[a][b] = v4i{0, 0, 0, 0};
+    const int nks = (L + 63) >> 6;
     for (int ks0 = wave; ks0 < nks; ks0 += SW * KB) {
-        v4i a[KB], b[KB];
+        v4i w[KB][FN], x[KB][FM];
 #pragma unroll
         for (int j = 0; j < KB; j++) {
-            const int k = (ks0 + j * SW) * 32 + kh;
-            a[j] = piece_load(P.wgt, wrow + k, wbytes);
-            b[j] = piece_load(P.act, arow + k, abytes);
+            const uint32_t k = (uint32_t)((ks0 + j * SW) * 64 + kh);
+#pragma unroll
+            for (int f = 0; f < FN; f++) w[j][f] = piece_load(P.wgt, wrow[f] + k, wbytes);
+#pragma unroll
+            for (int f = 0; f < FM; f++) x[j][f] = piece_load(P.act, arow[f] + k, abytes);
         }
 #pragma unroll
         for (int j = 0; j < KB; j++) {
-            const int k = (ks0 + j * SW) * 32 + kh;
-            a[j] = piece_cut<WHOLE>(a[j], P.wgt, wrow + k, wbytes, k, Lw);
-            b[j] = piece_cut<WHOLE>(b[j], P.act, arow + k, abytes, k, La);
+            const int k = (ks0 + j * SW) * 64 + kh;
+#pragma unroll
+            for (int f = 0; f < FN; f++) w[j][f] = piece_cut<WHOLE>(w[j][f], P.wgt, wrow[f] + k, wbytes, k, Lw[f]);
+#pragma unroll
+            for (int f = 0; f < FM; f++) x[j][f] = piece_cut<WHOLE>(x[j][f], P.act, arow[f] + k, abytes, k, La[f]);
         }
 #pragma unroll
-        for (int j = 0; j < KB; j++) acc = __builtin_amdgcn_mfma_i32_32x32x32_i8(a[j], b[j], acc, 0, 0, 0);
+        for (int j = 0; j < KB; j++)
+#pragma unroll
+            for (int a = 0; a < FN; a++)
+#pragma unroll
+                for (int b = 0; b < FM; b++)
+                    acc[a][b] = __builtin_amdgcn_mfma_i32_16x16x64_i8(w[j][a], x[j][b], acc[a][b], 0, 0, 0);
     }
 
-    // acc element 4*jj + i: channel n0 + 8*jj + 4*(lane/32) + i, row m0 + lane%32.
-    int32_t* mine = red + (wave * 32 + r32) * RP + 4 * (lane >> 5);
+    // acc[a][b] element i: channel n0 + 16 a + 4*(lane/16) + i, row m0 + 16 b + lane%16.
 #pragma unroll
-    for (int jj = 0; jj < 4; jj++) {
-        v4i q;
-        q[0] = acc[4 * jj];
-        q[1] = acc[4 * jj + 1];
-        q[2] = acc[4 * jj + 2];
-        q[3] = acc[4 * jj + 3];
-        *(v4i*)(mine + 8 * jj) = q;
-    }
+    for (int a = 0; a < FN; a++)
+#pragma unroll
+        for (int b = 0; b < FM; b++)
+            *(v4i*)(red + (wave * ROWS + 16 * b + r16) * RP + 16 * a + 4 * (lane >> 4)) = acc[a][b];
     __syncthreads();
-    if (threadIdx.x < 256) {
+    if (threadIdx.x < ROWS * 8) {
         const int row = threadIdx.x >> 3, c4 = (threadIdx.x & 7) * 4;
         const int m = m0 + row, n = n0 + c4;
         v4i s = *(const v4i*)(red + row * RP + c4);
 #pragma unroll
-        for (int w = 1; w < SW; w++) s += *(const v4i*)(red + (w * 32 + row) * RP + c4);
+        for (int w = 1; w < SW; w++) s += *(const v4i*)(red + (w * ROWS + row) * RP + c4);
         if (m < P.M && n < P.Nout) {
             const int nv = min(4, P.Nout - n);
             int32_t v[4] = {s[0], s[1], s[2], s[3]};
@@ -142,9 +162,9 @@ __device__ __forceinline__ void small_tile(const IgemmProblem& P, int tile, int3
 
 // Main launch: every tile once, the maximum folded in, the output rounded
 // with the shift of the previous call (none stored without a guess).
-template <bool WHOLE>
+template <bool WHOLE, int FM>
 __global__ __launch_bounds__(ST) void igemm_small_main(IgemmProblem P, IgemmCtl ctl) {
-    __shared__ __attribute__((aligned(16))) int32_t red[SW * 32 * RP];
+    __shared__ __attribute__((aligned(16))) int32_t red[SW * 16 * FM * RP];
     __shared__ uint32_t wmax[ST / 64];
     niti_stats* st = ctl.stats;
     const int slot = call_slot(st);
@@ -153,15 +173,15 @@ __global__ __launch_bounds__(ST) void igemm_small_main(IgemmProblem P, IgemmCtl 
     begin_call(st, slot, hint);
     const RoundK rk = make_round(hint < 0 ? 0 : hint, ctl.mode);
     uint32_t tmax = 0;
-    small_tile<WHOLE>(P, blockIdx.x, red, rk, ctl.relu, hint >= 0, true, tmax);
+    small_tile<WHOLE, FM>(P, blockIdx.x, red, rk, ctl.relu, hint >= 0, true, tmax);
     block_publish_max32(st, slot, tmax, wmax, snap);  // magnitudes <= 2^31
 }
 
 // Fix-up launch: with the final maximum, recompute every tile when the
 // guessed shift was wrong; workgroup 0 then finalizes the statistics.
-template <bool WHOLE>
+template <bool WHOLE, int FM>
 __global__ __launch_bounds__(ST) void igemm_small_fixup(IgemmProblem P, IgemmCtl ctl, int ntiles) {
-    __shared__ __attribute__((aligned(16))) int32_t red[SW * 32 * RP];
+    __shared__ __attribute__((aligned(16))) int32_t red[SW * 16 * FM * RP];
     niti_stats* st = ctl.stats;
     const CallState cs = shared_call_state(st);
     const int hint = cs.hint;
@@ -169,7 +189,7 @@ __global__ __launch_bounds__(ST) void igemm_small_fixup(IgemmProblem P, IgemmCtl
     if (bp != hint) {
         const RoundK rk = make_round(bp, ctl.mode);
         uint32_t dummy = 0;
-        for (int t = blockIdx.x; t < ntiles; t += gridDim.x) small_tile<WHOLE>(P, t, red, rk, ctl.relu, true, false, dummy);
+        for (int t = blockIdx.x; t < ntiles; t += gridDim.x) small_tile<WHOLE, FM>(P, t, red, rk, ctl.relu, true, false, dummy);
     }
     if (is_finisher()) finish_call(st, ctl.target, ctl.ex, ctl.static_flags, 1);
 }
@@ -193,22 +213,30 @@ bool igemm_small_eligible(const IgemmBatch& b) {
 }
 
 namespace {
-template <bool WHOLE>
+template <bool WHOLE, int FM>
 hipError_t launch_small(const IgemmProblem& p, const IgemmCtl& ctl, hipStream_t stream) {
-    const int ntiles = ((p.M + 31) / 32) * ((p.Nout + 31) / 32);
+    const int ntiles = ((p.M + 16 * FM - 1) / (16 * FM)) * ((p.Nout + 31) / 32);
     const int tk = timing_begin(NITI_TIMING_KERNEL, stream, "igemm_small_main");
-    hipLaunchKernelGGL(igemm_small_main<WHOLE>, dim3(ntiles), dim3(ST), 0, stream, p, ctl);
+    hipLaunchKernelGGL((igemm_small_main<WHOLE, FM>), dim3(ntiles), dim3(ST), 0, stream, p, ctl);
     timing_end(tk, stream);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     const int fix_grid = ntiles < kFixupGrid ? ntiles : kFixupGrid;
-    hipLaunchKernelGGL(igemm_small_fixup<WHOLE>, dim3(fix_grid), dim3(ST), 0, stream, p, ctl, ntiles);
+    hipLaunchKernelGGL((igemm_small_fixup<WHOLE, FM>), dim3(fix_grid), dim3(ST), 0, stream, p, ctl, ntiles);
     return hipGetLastError();
 }
 }  // namespace
 
+// 64 rows per tile read the weights half as often; taken where that still
+// leaves a workgroup per CU.  Training passes at batch 128 in us, 32 rows with
+// 32 x 32 x 32 MFMAs before / 32 rows / 64 rows: 4096 -> 4096 82.7 / 84.6 /
+// 76.2; 9216 -> 4096 140.5 / 138.5 / 130.4; 4096 -> 1000 89.9 / 87.0 / 78.4.
+// With 128 tiles of 64 rows, 64 x 4096 x 4096: 15.3 in 32 rows, 17.5 in 64.
 hipError_t igemm_small_run(IgemmBatch& b, IgemmCtl ctl, hipStream_t stream) {
-    return b.p[0].L % 16 == 0 ? launch_small<true>(b.p[0], ctl, stream) : launch_small<false>(b.p[0], ctl, stream);
+    const IgemmProblem& p = b.p[0];
+    const bool tall = p.M > 32 && (int64_t)((p.M + 63) / 64) * ((p.Nout + 31) / 32) >= 256;
+    if (p.L % 16 == 0) return tall ? launch_small<true, 4>(p, ctl, stream) : launch_small<true, 2>(p, ctl, stream);
+    return tall ? launch_small<false, 4>(p, ctl, stream) : launch_small<false, 2>(p, ctl, stream);
 }
 
 }  // namespace niti

@@ -17,6 +17,8 @@ GEMMS = [
     (1, 1, 15, False, oracle.PSR), (3, 2, 17, True, oracle.PSR), (5, 33, 31, False, oracle.RTN),
     (40, 70, 1111, True, oracle.PSR), (1025, 1029, 1, False, oracle.PSR), (1030, 64, 63, True, oracle.SR),
     (1100, 1500, 1111, True, oracle.PSR), (1920, 2176, 65, False, oracle.PSR), (2049, 2040, 257, True, oracle.RTN),
+    (33, 8190, 48, True, oracle.PSR), (100, 4104, 33, False, oracle.PSR), (130, 2800, 1090, True, oracle.RTN),  # 64 rows
+    (1000, 520, 64, False, oracle.PSR), (64, 8161, 129, True, oracle.PSR),
     (1111, 70, 321, False, oracle.SR), (2048, 2176, 127, False, oracle.SR),
 ]
 
