@@ -438,27 +438,10 @@ struct ExpArgs {
     int8_t* s_out;      // output exponent (or NULL: not formed)
 };
 
-// The running level of a block's maximum: the bitwidth with the leading bits
-// of the fraction below it (8 fraction bits; linear between powers of two),
-// moved a quarter of the way to each new maximum, all the way when it is more
-// than an octave and a half off.  It settles exactly on a constant maximum from
-// either side.  In training a maximum often lies near a power of two and its
-// bitwidth flips from step to step; the level's bitwidth then misses less
-// often than the last one's (VGG-small-7 at batch 256, 400 steps: 29% of the
-// forward and back-propagation calls against 37%; LeNet-5 22% against 29%).
-__device__ __forceinline__ int32_t next_level(int32_t level, uint64_t mx) {
-    if (mx == 0) return level;
-    const int b = bitlen64(mx);
-    const int32_t now = (b << 8) | (int32_t)((b > 8 ? mx >> (b - 9) : mx << (9 - b)) & 0xFF);
-    const int32_t d = now - level;
-    if (level == 0 || d >= 384 || d <= -384) return now;
-    return level + ((d + (d > 0 ? 3 : 0)) >> 2);
-}
-
 // The finishing launch's single thread: derive b and bp from the tensor
 // maximum, form the output exponent (Algorithm 2: s_q = s_q32 + bp), record
-// the statistics, form the next call's first guess, clear the other slot and
-// count the call.
+// the statistics, make bp the next call's first guess, clear the other
+// slot and count the call.
 // Every value it reads is loaded before any is used (one memory round trip).
 // max_shift: the maximum was folded in shifted right by that many bits (its
 // effective bitwidth is then bitlen + max_shift; see the integer loss).
@@ -470,7 +453,6 @@ __device__ inline void finish_call(niti_stats* st, int target, ExpArgs ex, uint3
     const int cur = st->cur & 1;
     const int hint_used = st->hint_used;
     const uint32_t misses = st->misses, calls = st->calls;
-    const int32_t level0 = st->level;
     const int sa = ex.s_out && ex.s_a ? (int)*ex.s_a : 0;
     const int sb = ex.s_out && ex.s_b ? (int)*ex.s_b : 0;
     const uint64_t mx = cur ? a1 : a0;
@@ -494,10 +476,7 @@ __device__ inline void finish_call(niti_stats* st, int target, ExpArgs ex, uint3
     st->bp = bp;
     st->flags = (int32_t)fl;
     st->s_out = s;
-    const int32_t level = next_level(level0, mx);
-    const int lb = (level >> 8) + max_shift;
-    st->level = level;
-    st->bp_hint = mx == 0 ? bp : (lb > target ? lb - target : 0);
+    st->bp_hint = bp;
     st->acc_max[cur ^ 1] = 0;
     st->wflags[cur ^ 1] = 0;
     st->calls = calls + 1;
