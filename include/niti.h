@@ -52,10 +52,11 @@
  *               rounded magnitude that would reach 128 is held at 127, so
  *               outputs lie in [-127, 127].
  *   Speculation The library first rounds with the binary point that the
- *               same stats block reported last time (bp_hint), checks it
- *               against the true block maximum, and recomputes the output
- *               when they differ.  Results are identical either way; a
- *               miss only costs time and sets NITI_FLAG_HINT_MISS.
+ *               maxima of the same stats block's earlier calls suggest
+ *               (bp_hint), checks it against the true block maximum, and
+ *               recomputes the output when they differ.  Results are
+ *               identical either way; a miss only costs time and sets
+ *               NITI_FLAG_HINT_MISS.
  */
 #ifndef NITI_H
 #define NITI_H
@@ -113,7 +114,9 @@ typedef struct niti_stats {
     int32_t hint_used;   /* guess the call in progress tried */
     uint64_t sr_seed;    /* in: seed of the NITI_ROUND_SR draws (zero-filled is seed 0) */
     uint32_t sr_call;    /* draw index c of the call in progress */
-    uint32_t reserved[11];
+    int32_t level;       /* running level of the maximum's bitwidth, 8 fraction bits (0: none yet) */
+    int32_t trust;       /* above 0: the level has predicted better than the last call, -3..3 */
+    uint32_t reserved[9];
 } niti_stats;
 
 /* Convolution geometry.  Input x is NHWC [n][h][w][c]; filter is KRSC

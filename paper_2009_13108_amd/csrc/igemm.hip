@@ -20,7 +20,7 @@
 // whole output tensor, which is known only when every tile is done.  The
 // main launch computes every tile, folds its maximum into the
 // tensor maximum and writes the tile rounded with the shift the same stats
-// block reported last time.  The fix-up launch derives the
+// block suggests (niti_device.h, finish_call).  The fix-up launch derives the
 // true shift; when it matches, the output is already exact and the launch
 // only finalizes the statistics; otherwise it recomputes every tile with the
 // true shift.  Either way the result equals rounding the true accumulators

@@ -438,10 +438,30 @@ struct ExpArgs {
     int8_t* s_out;      // output exponent (or NULL: not formed)
 };
 
+// The next call's first guess is the last binary point, or that of the
+// maximum's running level where that has been the better guess.  The level is
+// the bitwidth with the leading bits of the fraction below it (8 fraction
+// bits; linear between powers of two), moved a quarter of the way to each new
+// maximum, all the way when it is more than an octave and a half off.  A
+// maximum that lies near a power of two flips its bitwidth from step to step,
+// and the level misses less; one that drifts is followed better by the last
+// call.  trust counts which of the two was right when they differed.
+// Misses of the forward and back-propagation calls, last / level / both:
+// VGG-small-7 at batch 256, 400 steps 37 / 29 / 30%; LeNet-5 29 / 22 / 23%; the
+// first 25 steps of a ResNet-18 layer set 3 / 19 / 3%.
+__device__ __forceinline__ int32_t next_level(int32_t level, uint64_t mx) {
+    if (mx == 0) return level;
+    const int b = bitlen64(mx);
+    const int32_t now = (b << 8) | (int32_t)((b > 8 ? mx >> (b - 9) : mx << (9 - b)) & 0xFF);
+    const int32_t d = now - level;
+    if (level == 0 || d >= 384 || d <= -384) return now;
+    return level + ((d + (d > 0 ? 3 : 0)) >> 2);
+}
+
 // The finishing launch's single thread: derive b and bp from the tensor
 // maximum, form the output exponent (Algorithm 2: s_q = s_q32 + bp), record
-// the statistics, make bp the next call's first guess, clear the other
-// slot and count the call.
+// the statistics, form the next call's first guess, clear the other slot and
+// count the call.
 // Every value it reads is loaded before any is used (one memory round trip).
 // max_shift: the maximum was folded in shifted right by that many bits (its
 // effective bitwidth is then bitlen + max_shift; see the integer loss).
@@ -453,6 +473,7 @@ __device__ inline void finish_call(niti_stats* st, int target, ExpArgs ex, uint3
     const int cur = st->cur & 1;
     const int hint_used = st->hint_used;
     const uint32_t misses = st->misses, calls = st->calls;
+    const int32_t level0 = st->level, trust0 = st->trust, bp0 = st->bp;
     const int sa = ex.s_out && ex.s_a ? (int)*ex.s_a : 0;
     const int sb = ex.s_out && ex.s_b ? (int)*ex.s_b : 0;
     const uint64_t mx = cur ? a1 : a0;
@@ -476,7 +497,16 @@ __device__ inline void finish_call(niti_stats* st, int target, ExpArgs ex, uint3
     st->bp = bp;
     st->flags = (int32_t)fl;
     st->s_out = s;
-    st->bp_hint = bp;
+    const int32_t level = next_level(level0, mx);
+    const int lb0 = (level0 >> 8) + max_shift, lb = (level >> 8) + max_shift;
+    const int was = lb0 > target ? lb0 - target : 0;   // what the level would have guessed for this call
+    const int32_t trust = was == bp0 || calls == 0 ? trust0
+                          : was == bp              ? min(trust0 + 1, 3)
+                          : bp0 == bp              ? max(trust0 - 1, -3)
+                                                   : trust0;
+    st->level = level;
+    st->trust = trust;
+    st->bp_hint = trust > 0 && mx != 0 ? (lb > target ? lb - target : 0) : bp;
     st->acc_max[cur ^ 1] = 0;
     st->wflags[cur ^ 1] = 0;
     st->calls = calls + 1;
