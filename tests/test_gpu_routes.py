@@ -1,0 +1,53 @@
+"""Which kernel a call runs, read from the library's timing records, on both
+sides of each rule that chooses by size.  The results are exact whichever
+kernel runs (the parity tests compare them at these sizes and others); these
+cases keep a rule from moving over shapes where its kernel is the slower one."""
+import pytest
+
+from paper_2009_13108_amd import niti
+from helpers import say
+
+pytestmark = pytest.mark.gpu
+
+
+def kernels(call):
+    """Labels of the contraction launches and split sums of one call."""
+    import torch
+    niti.timing_enable(True)
+    call()
+    niti.timing_enable(False)
+    torch.cuda.synchronize()
+    return [name for fam, name, _ in niti.timing_records() if fam in (niti.TIMING_KERNEL, niti.TIMING_SUM)]
+
+
+def i8(*shape):
+    import torch
+    return torch.ones(shape, dtype=torch.int8, device="cuda")
+
+
+def run_gemm(M, N, K, mode=niti.PSR):
+    return kernels(lambda: niti.gemm_fwd(i8(M, K), i8(N, K), i8(M, N), niti.new_stats(), mode=mode))
+
+
+def run_conv(op, n, h, c, k, r, stride, pad, mode=niti.PSR):
+    d = niti.ConvDesc.make(n, h, h, c, k, r, r, stride, pad)
+    x, w, y, stats = i8(*d.x_shape()), i8(*d.w_shape()), i8(*d.y_shape()), niti.new_stats()
+    ws = niti.new_workspace(niti.workspace_bytes(
+        {"fwd": niti.OP_CONV_FWD, "bwd": niti.OP_CONV_BWD_DATA, "wgrad": niti.OP_CONV_BWD_WEIGHT}[op], d))
+    if op == "fwd":
+        return kernels(lambda: niti.conv_fwd(d, x, w, y, stats, mode=mode, ws=ws))
+    if op == "bwd":
+        return kernels(lambda: niti.conv_bwd_data(d, y, w, x, stats, ws, mode=mode))
+    return kernels(lambda: niti.conv_bwd_weight(d, x, y, w, stats, ws, mode=mode))
+
+
+GATHERED = ["wgrad_small_kernel"] * 2
+
+
+@pytest.mark.parametrize("case", [
+    # n, h, c, k, r, stride, pad, mode, launches
+    (64, 1, 512, 512, 1, 1, 0, niti.PSR, GATHERED),       # 256 tiles of 32 x 32
+], ids=str)
+def test_gathered_weight_gradient(case):
+    say("gathered", case)
+    assert run_conv("wgrad", *case[:8]) == case[8]
