@@ -559,16 +559,29 @@ WgradPlan wgrad_tap_plan(const WgradProblem& p) {
     pl.tbk = 64;
     const int64_t tiles = (K / 64) * (C / CW);
     const int64_t steps = (npix + PIX - 1) / PIX;
-    // Workgroups to aim for, at least two stages each.  A workgroup holds most
+    // About 192 workgroups, at least two stages each.  A workgroup holds most
     // of its CU's LDS and registers, so a grid of one per CU shuts out a
     // kernel running beside it on another stream (the back-propagation of a
     // training step).  Shared rows leave a quarter of the CUs free: one per CU
-    // gained 1% in a layer alone and lost 1 to 2% in two-stream steps.  The
-    // nine-run form is slower, and idle CUs cost it more: the strided 28x28,
-    // 128 -> 256 layer's training pass took 89.2 us at 192 and 83.8 at 256,
-    // and a ResNet-18 layer-set step on two streams 1.685 and 1.679 ms.
-    const int64_t groups = shared_rows(p) ? 192 : 256;
-    int64_t splits = (groups + tiles - 1) / tiles;
+    // gained 1% in a layer alone and lost 1 to 2% in two-stream steps.
+    int64_t splits = (192 + tiles - 1) / tiles;
+    // The nine-run form is slower, and idle CUs cost it more, so it takes as
+    // many ranges as fit in one round of one workgroup per CU, where a range
+    // keeps 13 stages: shorter ones lose more to the partial sums (written and
+    // read again) than they gain.  Nine or more ranges take the slower of the
+    // two sum kernels, so a step from eight or fewer to more than eight needs
+    // 23.  Weight gradients alone, in us, with three quarters of the CUs / one
+    // full round: 128 -> 128 channels at 56x56, stride 2, batch 256 (24 / 32
+    // ranges) 100.5 / 82.8; 128 -> 512 at 28x28, stride 2, batch 128 (6 / 8)
+    // 60.3 / 50.5; but 256 -> 128 at 14x14, stride 2, batch 100 (10 / 13) 23.0 /
+    // 26.6, and 64 -> 64 at 28x28, batch 100 (88 / 123) 23.6 / 25.5.  A second
+    // round of a few workgroups costs most: 320 -> 512 at 14x14, stride 2,
+    // batch 128, 240 / 320 workgroups 41.4 / 56.2.
+    if (!shared_rows(p)) {
+        const int64_t full = 256 / tiles;
+        const int64_t stages = full > 0 ? (steps + full - 1) / full : 0;
+        if (full > splits && stages >= 13 && (stages >= 23 || splits > 8 || full <= 8)) splits = full;
+    }
     const int64_t max_splits = steps / 2 > 1 ? steps / 2 : 1;
     if (splits > max_splits) splits = max_splits;
     if (splits < 1) splits = 1;
