@@ -28,7 +28,6 @@ constexpr int SW = 8;            // waves per workgroup (sample slices)
 constexpr int ST = SW * 64;
 constexpr int RP = 36;           // LDS row pitch of a partial tile (ints; 16-byte aligned)
 constexpr int kMaxPix = 1024;    // eligibility: at most this many samples
-constexpr int kMaxTiles = 1024;  // and 32 x 32 tiles
 
 // 16 samples from p of column col (both in range after clamping), zero for
 // samples at or past n or when col_ok is false.
@@ -111,12 +110,21 @@ __global__ __launch_bounds__(ST) void wgrad_small_kernel(WgradProblem P, int8_t*
 }  // namespace
 
 // Plain products (1 x 1 filter, no padding, no stride): x and dy are matrices
-// with one row per sample.  Above 1024 samples or tiles the byte gathers
-// outweigh the launches saved, and the LDS-staged kernels are used.
+// with one row per sample.  The byte gathers issue 32 loads per MFMA, twice, so
+// the launches saved pay for one tile per CU and no more where the LDS-staged
+// DMA kernel can run (channels in whole 16s).  Whole calls in us, gathered /
+// DMA kernel: 464 x 544 weights and 21 samples (255 tiles) 8.9 / 9.4; 1168 x
+// 368, 53 samples (444 tiles) 15.0 / 9.5; 1264 x 512, 1003 samples (640) 26.7 /
+// 17.5; 4352 x 224, 17 samples (952) 23.5 / 9.8.  The general kernel, which
+// takes the other channel counts, gathers too and walks its samples in steps:
+// 480 tiles and 105 samples 11.4 / 20.2, 594 tiles and 28 samples 16.3 / 15.3,
+// 1000 tiles and 10 samples 25.0 / 16.2, 896 tiles and 167 samples 15.7 / 27.3.
 bool wgrad_small_eligible(const WgradProblem& p) {
     if (p.win || p.R != 1 || p.S != 1 || p.sh != 1 || p.sw != 1 || p.ph != 0 || p.pw != 0) return false;
     if (p.H != p.P || p.W != p.Q || p.npix < 1 || p.npix > kMaxPix || p.C % 4 != 0) return false;
-    return (int64_t)((p.C + 31) / 32) * ((p.K + 31) / 32) <= kMaxTiles;
+    const int64_t tiles = (int64_t)((p.C + 31) / 32) * ((p.K + 31) / 32);
+    if (wgrad_dma_eligible(p)) return tiles <= 256;
+    return tiles <= (p.npix >= 128 ? 1024 : 512);
 }
 
 hipError_t wgrad_small_run(WgradProblem& p, int8_t* w, int32_t* g32, int mu, int mode, niti_stats* st,

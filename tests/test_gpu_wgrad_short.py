@@ -22,8 +22,14 @@ CASES = [
     (3, 5, 7, 12, 40, oracle.PSR, 5),            # a 1 x 1 convolution
     (1024, 1, 1, 32, 64, oracle.PSR, 8),         # the most samples of the gathered form
     (1025, 1, 1, 32, 64, oracle.PSR, 1),         # one more
-    (8, 1, 1, 1024, 1024, oracle.SR, 5),         # the most tiles of the gathered form
-    (8, 1, 1, 1040, 1024, oracle.PSR, 5),        # one column of tiles more: formed twice through LDS
+    (8, 1, 1, 512, 512, oracle.SR, 5),           # the most tiles of the gathered form in whole 16s
+    (8, 1, 1, 528, 512, oracle.PSR, 5),          # one column of tiles more: through LDS
+    (9, 1, 1, 2720, 166, oracle.RTN, 5),         # the other channel counts: 510 tiles, below 128 samples
+    (9, 1, 1, 2752, 166, oracle.SR, 5),          # 516: the general kernel
+    (128, 1, 1, 5460, 166, oracle.PSR, 5),       # 1026, 128 samples: the general kernel
+    (128, 1, 1, 5428, 166, oracle.PSR, 5),       # 1020: gathered
+    (8, 1, 1, 1024, 1024, oracle.SR, 5),
+    (8, 1, 1, 1040, 1024, oracle.PSR, 5),
     (70, 1, 1, 2064, 528, oracle.RTN, 4),        # ragged tiles and stages
     (65, 1, 1, 1056, 1008, oracle.SR, 5),
     (512, 1, 1, 1296, 816, oracle.PSR, 5),       # the most samples of that form
