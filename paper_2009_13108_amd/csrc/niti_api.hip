@@ -549,7 +549,7 @@ niti_status niti_conv_bwd_weight(const niti_conv_desc* d, const int8_t* x, const
         timing_end(t, strm);
         return hip_status(e);
     }
-    if (!g32_out && !ws_.tap && wgrad_twice_eligible(p, plan)) {
+    if (!g32_out && !ws_.tap && wgrad_twice_eligible(p, plan, mode)) {
         const int t = timing_begin(NITI_TIMING_WGRAD, strm);
         e = wgrad_twice_run(p, plan, w, mu, mode, stats, acc_flags(npix), strm);
         timing_end(t, strm);

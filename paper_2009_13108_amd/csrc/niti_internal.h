@@ -128,7 +128,7 @@ bool wgrad_dma_eligible(const WgradProblem& p);
 hipError_t wgrad_dma_run(WgradProblem& p, const WgradPlan& plan, hipStream_t stream);
 // The whole call (contraction, maximum, update) of a one-range plan in two
 // launches of the DMA kernel, without g32 in memory (wgrad_dma.hip).
-bool wgrad_twice_eligible(const WgradProblem& p, const WgradPlan& plan);
+bool wgrad_twice_eligible(const WgradProblem& p, const WgradPlan& plan, int mode);
 hipError_t wgrad_twice_run(WgradProblem& p, const WgradPlan& plan, int8_t* w, int mu, int mode, niti_stats* st,
                            uint32_t static_flags, hipStream_t stream);
 // The whole call of a small fully-connected layer in two launches

@@ -435,22 +435,31 @@ hipError_t wgrad_dma_run(WgradProblem& p, const WgradPlan& plan, hipStream_t str
     return launch<128, 128, 4, kStore>(p, plan, stream);
 }
 
-// Running the contraction again costs its 2 npix operations per weight once
-// more and saves the int32 gradient's round trips: 12 bytes per weight
-// (written, read for the maximum, read for the update).  At this kernel's
-// ~1 POPS against ~5 TB/s that is even near 1000 samples; 512 leaves a margin.
-// 4096 -> 4096, 128 samples (16.8 M weights): 61.0 us as contraction, maximum
-// and update, 31.4 us this way (13.0 + 18.5; the update's share is bound by
-// the ~14 vector instructions per weight next to the 33.5 MB it moves).
-bool wgrad_twice_eligible(const WgradProblem& p, const WgradPlan& plan) {
-    return plan.splits == 1 && !p.win && p.npix <= 512 && wgrad_dma_eligible(p);
+// Running the contraction again costs its 2 npix operations per weight and its
+// latency once more, on as many CUs as it has tiles, and saves the int32
+// gradient's round trips: 12 bytes per weight (written, read for the maximum,
+// read for the update) by kernels that always fill the chip.  So it pays from a
+// number of weights on that grows with the samples.  Stochastic rounding's 64-bit
+// draws are the dearer part of the epilogue on few CUs, and with 32 channels or
+// fewer most of a tile's epilogue is for rows that do not exist.  The limits
+// are the best of a grid over 285 (94 for stochastic rounding) random layers:
+// at most 9% (14%) off the better form.  Whole calls in us, stored / twice:
+// 4096 -> 4096, 128 samples 61.0 / 31.4; 1808 -> 720, 53 samples 18.3 / 10.6;
+// 304 -> 48, 464 samples 9.6 / 11.6; 80 -> 448, 294 samples, stochastic 10.3 /
+// 14.9; 8256 -> 16, 5x5, 98 pixels, stochastic 27.7 / 33.5; 5616 -> 16, 3x3, 240
+// pixels 14.8 / 16.0.
+bool wgrad_twice_eligible(const WgradProblem& p, const WgradPlan& plan, int mode) {
+    if (plan.splits != 1 || p.win || p.npix > 512 || p.K <= 32 || !wgrad_dma_eligible(p)) return false;
+    const int64_t weights = (int64_t)p.K * p.ncol;
+    return mode == NITI_ROUND_SR ? weights >= (1 << 17) + (int64_t)2048 * p.npix
+                                 : weights >= (1 << 15) + (int64_t)512 * p.npix;
 }
 
 hipError_t wgrad_twice_run(WgradProblem& p, const WgradPlan& plan, int8_t* w, int mu, int mode, niti_stats* st,
                            uint32_t static_flags, hipStream_t stream) {
     p.chunk = plan.chunk;
-    // Three stages: the whole ring of a batch of 128 is in flight at once, and
-    // the 48 KB let three workgroups share a CU instead of two.
+    // Three stages: a batch of 128 samples is two, so the whole reduction is in
+    // flight at once and a fourth would only load zeros.
     const WgradFinish fin{w, st, mu, static_flags};
 #define NITI_TWICE(EP) (plan.tbk == 64 ? launch<64, 128, 3, EP>(p, plan, stream, fin) : launch<128, 128, 3, EP>(p, plan, stream, fin))
     hipError_t e = NITI_TWICE(kMaxOnly);

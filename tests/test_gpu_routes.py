@@ -43,6 +43,7 @@ def run_conv(op, n, h, c, k, r, stride, pad, mode=niti.PSR):
 
 GATHERED = ["wgrad_small_kernel"] * 2
 TWICE = ["wgrad_dma_kernel<128,128,3>"] * 2
+STORED = ["wgrad_dma_kernel<128,128,4>", "split_sum<1>"]
 
 
 @pytest.mark.parametrize("case", [
@@ -62,3 +63,18 @@ def test_gathered_weight_gradient(case):
         assert "wgrad_small_kernel" not in got, got
     else:
         assert got == case[8]
+
+
+@pytest.mark.parametrize("case", [
+    (16, 1, 1056, 1008, 1, 1, 0, niti.PSR, TWICE),
+    (16, 1, 1056, 1008, 1, 1, 0, niti.SR, TWICE),
+    (8, 13, 32, 192, 5, 2, 2, niti.SR, STORED),           # 153600 weights, 392 pixels
+    (8, 13, 32, 192, 5, 2, 2, niti.PSR, STORED),
+    (1, 13, 32, 192, 5, 2, 2, niti.PSR, TWICE),           # 49 pixels
+    (1, 13, 32, 192, 5, 2, 2, niti.SR, STORED),
+    (16, 1, 16400, 32, 1, 1, 0, niti.PSR, ["wgrad_dma_kernel<64,128,4>", "split_sum<1>"]),
+    (16, 1, 16400, 48, 1, 1, 0, niti.PSR, ["wgrad_dma_kernel<64,128,3>"] * 2),
+], ids=str)
+def test_weight_gradient_formed_twice(case):
+    say("twice", case)
+    assert run_conv("wgrad", *case[:8]) == case[8]
