@@ -30,16 +30,17 @@ constexpr int MAX_M = 1024;           // eligibility: at most this many output r
 
 // An operand's 16-byte piece is loaded from offset off, moved into the tensor
 // where it would pass the end, without a branch, so that all pieces of a batch
-// are in flight at once; piece_cut then zeroes what lies past L and, for the
-// moved ones, gathers the bytes singly.  Rows whose length is a multiple of 16
-// (WHOLE) need only the zeroing.  bytes >= 16.
+// are in flight at once.  bytes >= 16.
 __device__ __forceinline__ v4i piece_load(const int8_t* base, uint32_t off, uint32_t bytes) {
     return __builtin_bit_cast(v4i, load16_any(base + min(off, bytes - 16)));
 }
+// A piece of the last step: zeros past L and, where the load was moved, the
+// bytes gathered singly.  Rows whose length is a multiple of 16 (WHOLE) need
+// only the zeroing, earlier steps none of it.
 template <bool WHOLE>
 __device__ __forceinline__ v4i piece_cut(v4i v, const int8_t* base, uint32_t off, uint32_t bytes, int k, int L) {
     if (k >= L) return v4i{0, 0, 0, 0};
-    if (!WHOLE && (k + 16 > L || off + 16 > bytes)) {
+    if (!WHOLE && k + 16 > L) {
         if (off + 16 <= bytes) return __builtin_bit_cast(v4i, keep_bytes(__builtin_bit_cast(uint4, v), 0, L - k));
         const int n = min(16, L - k);
         uint32_t w[4] = {0u, 0u, 0u, 0u};
@@ -66,21 +67,18 @@ __device__ __forceinline__ void small_tile(const IgemmProblem& P, int tile, int3
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int r16 = lane & 15, kh = (lane >> 4) * 16;
     const int L = P.L;
-    // Operand rows of this lane (clamped into the tensor; rows past the edge
-    // load zeros).
+    // Operand rows of this lane.  Rows past the edge read the first one: what
+    // they give is neither stored nor part of the maximum.
     uint32_t wrow[FN], arow[FM];
-    int Lw[FN], La[FM];
 #pragma unroll
     for (int f = 0; f < FN; f++) {
         const int n = n0 + 16 * f + r16;
         wrow[f] = (uint32_t)(n < P.Nout ? n : 0) * (uint32_t)L;
-        Lw[f] = n < P.Nout ? L : 0;
     }
 #pragma unroll
     for (int f = 0; f < FM; f++) {
         const int m = m0 + 16 * f + r16;
         arow[f] = (uint32_t)(m < P.M ? m : 0) * (uint32_t)L;
-        La[f] = m < P.M ? L : 0;
     }
     const uint32_t wbytes = (uint32_t)P.wgt_bytes, abytes = (uint32_t)P.act_bytes;
 
@@ -104,11 +102,13 @@ __device__ __forceinline__ void small_tile(const IgemmProblem& P, int tile, int3
 #pragma unroll
         for (int j = 0; j < KB; j++) {
             if (ks0 + j * SW >= nks) break;
-            const int k = (ks0 + j * SW) * 64 + kh;
+            if (ks0 + j * SW == nks - 1) {   // uniform
+                const int k = (ks0 + j * SW) * 64 + kh;
 #pragma unroll
-            for (int f = 0; f < FN; f++) w[j][f] = piece_cut<WHOLE>(w[j][f], P.wgt, wrow[f] + k, wbytes, k, Lw[f]);
+                for (int f = 0; f < FN; f++) w[j][f] = piece_cut<WHOLE>(w[j][f], P.wgt, wrow[f] + k, wbytes, k, L);
 #pragma unroll
-            for (int f = 0; f < FM; f++) x[j][f] = piece_cut<WHOLE>(x[j][f], P.act, arow[f] + k, abytes, k, La[f]);
+                for (int f = 0; f < FM; f++) x[j][f] = piece_cut<WHOLE>(x[j][f], P.act, arow[f] + k, abytes, k, L);
+            }
 #pragma unroll
             for (int a = 0; a < FN; a++)
 #pragma unroll
@@ -219,7 +219,8 @@ namespace {
 template <bool WHOLE, int FM>
 hipError_t launch_small(const IgemmProblem& p, const IgemmCtl& ctl, hipStream_t stream) {
     const int ntiles = ((p.M + 16 * FM - 1) / (16 * FM)) * ((p.Nout + 31) / 32);
-    const int tk = timing_begin(NITI_TIMING_KERNEL, stream, "igemm_small_main");
+    const int tk = timing_on() ? timing_begin(NITI_TIMING_KERNEL, stream, kernel_label("igemm_small_main<%d,%d>", (int)WHOLE, FM))
+                               : -1;
     hipLaunchKernelGGL((igemm_small_main<WHOLE, FM>), dim3(ntiles), dim3(ST), 0, stream, p, ctl);
     timing_end(tk, stream);
     hipError_t e = hipGetLastError();
@@ -230,14 +231,16 @@ hipError_t launch_small(const IgemmProblem& p, const IgemmCtl& ctl, hipStream_t 
 }
 }  // namespace
 
-// 64 rows per tile read the weights half as often; taken where that still
-// leaves a workgroup per CU.  Training passes at batch 128 in us, 32 rows with
-// 32 x 32 x 32 MFMAs before / 32 rows / 64 rows: 4096 -> 4096 82.7 / 84.6 /
-// 76.2; 9216 -> 4096 140.5 / 138.5 / 130.4; 4096 -> 1000 89.9 / 87.0 / 78.4.
-// With 128 tiles of 64 rows, 64 x 4096 x 4096: 15.3 in 32 rows, 17.5 in 64.
+// 64 rows per tile read the weights half as often; taken where tiles of 32
+// rows are more than one per CU, so that a second round of them would follow.
+// Products in us, tiles of 32 / 64 rows: 64 x 4096 x 4096 (256 tiles of 32)
+// 15.3 / 17.5, 63 x 2645 x 4192 (166) 12.3 / 13.8; 67 x 2765 x 200 (261) 10.7 /
+// 8.4, 353 x 1084 x 2588 (408) 20.2 / 13.1, 44 x 6541 x 1844 (410) 19.6 / 12.5.
+// Training passes at batch 128, 32 rows / 64 rows: 4096 -> 4096 84.6 / 76.2;
+// 9216 -> 4096 138.5 / 130.4; 4096 -> 1000 87.0 / 78.4.
 hipError_t igemm_small_run(IgemmBatch& b, IgemmCtl ctl, hipStream_t stream) {
     const IgemmProblem& p = b.p[0];
-    const bool tall = p.M > 32 && (int64_t)((p.M + 63) / 64) * ((p.Nout + 31) / 32) >= 256;
+    const bool tall = p.M > 32 && (int64_t)((p.M + 31) / 32) * ((p.Nout + 31) / 32) > 256;
     if (p.L % 16 == 0) return tall ? launch_small<true, 4>(p, ctl, stream) : launch_small<true, 2>(p, ctl, stream);
     return tall ? launch_small<false, 4>(p, ctl, stream) : launch_small<false, 2>(p, ctl, stream);
 }

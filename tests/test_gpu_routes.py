@@ -78,3 +78,14 @@ def test_gathered_weight_gradient(case):
 def test_weight_gradient_formed_twice(case):
     say("twice", case)
     assert run_conv("wgrad", *case[:8]) == case[8]
+
+
+@pytest.mark.parametrize("case", [
+    (64, 4096, 4096, ["igemm_small_main<1,2>"]),           # 256 tiles of 32 rows: one per CU
+    (33, 4128, 256, ["igemm_small_main<1,4>"]),            # 258
+    (44, 6541, 1844, ["igemm_small_main<0,4>"]),
+    (32, 8000, 256, ["igemm_small_main<1,2>"]),            # no second 32 rows
+], ids=str)
+def test_small_product_rows(case):
+    say("small product", case)
+    assert run_gemm(*case[:3]) == case[3]

@@ -17,8 +17,11 @@ GEMMS = [
     (1, 1, 15, False, oracle.PSR), (3, 2, 17, True, oracle.PSR), (5, 33, 31, False, oracle.RTN),
     (40, 70, 1111, True, oracle.PSR), (1025, 1029, 1, False, oracle.PSR), (1030, 64, 63, True, oracle.SR),
     (1100, 1500, 1111, True, oracle.PSR), (1920, 2176, 65, False, oracle.PSR), (2049, 2040, 257, True, oracle.RTN),
-    (33, 8190, 48, True, oracle.PSR), (100, 4104, 33, False, oracle.PSR), (130, 2800, 1090, True, oracle.RTN),  # 64 rows
-    (1000, 520, 64, False, oracle.PSR), (64, 8161, 129, True, oracle.PSR),
+    # small products in 64 rows: one batch of loads, then two and three (2048 bytes each), the last one ragged
+    (33, 8064, 48, True, oracle.PSR), (100, 4104, 33, False, oracle.PSR), (130, 2600, 1090, True, oracle.RTN),
+    (1000, 520, 64, False, oracle.PSR), (64, 8060, 129, True, oracle.PSR),
+    (128, 4096, 4112, True, oracle.PSR), (130, 2600, 2200, False, oracle.RTN), (65, 4101, 2047, True, oracle.PSR),
+    (33, 4130, 2049, False, oracle.PSR),
     (1111, 70, 321, False, oracle.SR), (2048, 2176, 127, False, oracle.SR),
 ]
 
