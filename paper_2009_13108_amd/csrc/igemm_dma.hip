@@ -632,14 +632,18 @@ hipError_t run_mode(IgemmBatch& b, IgemmCtl ctl, hipStream_t stream) {
         tiles128 += (int64_t)((b.p[i].M + 127) / 128) * ((b.p[i].Nout + 127) / 128);
     }
     // K steps of 128 bytes where a step is uniform (rows, or channels in whole
-    // 128s) and there is more than one 128 x 128 tile per CU; windows and
-    // carried pieces stay at 64.  Measured in us at 64 / 128: 14x14, 256
-    // channels, batch 128 (training pass) 104.0 / 97.7; 8192^3 421 / 404;
-    // 4096^3 63.3 / 61.3; but 7x7, 512 channels (196 tiles, one per CU and a
-    // deep ring either way) 97.1 / 97.1, 2048^3 18.8 / 19.5, and 5x5, 96
-    // channels (carried pieces) 272 / 287.
-    bool step128 = (MODE == kGemm || MODE == kConv) && tiles128 > 256;
-    for (int i = 0; i < b.nprob; i++) step128 = step128 && (MODE != kConv || b.p[i].C % 128 == 0);
+    // 128s), the reduction is more than one step of 64 and there is more than
+    // one 128 x 128 tile per CU; windows and carried pieces stay at 64.
+    // Measured in us at 64 / 128: 14x14, 256 channels, batch 128 (training pass)
+    // 104.0 / 97.7; 8192^3 421 / 404; 4096^3 63.3 / 61.3; but 7x7, 512 channels
+    // (196 tiles, one per CU and a deep ring either way) 97.1 / 97.1, 2048^3
+    // 18.8 / 19.5, and 5x5, 96 channels (carried pieces) 272 / 287.  One step:
+    // 16930 x 192 x 64 9.9 / 10.7.  Tiles of 64 columns gain nothing from the
+    // longer rows and lose the ring's depth (four stages against two): 50176 x
+    // 64 x 3456 27.9 / 31.1, x 2304 23.3 / 25.7, 35105 x 42 x 1024 15.4 / 16.4.
+    bool step128 = (MODE == kGemm || MODE == kConv) && maxN > 64 && tiles128 > 256;
+    for (int i = 0; i < b.nprob; i++)
+        step128 = step128 && b.p[i].Ktot > 64 && (MODE != kConv || b.p[i].C % 128 == 0);
     // 256 x 256 tiles where they give most compute units a workgroup and pad
     // the channels no further than 128 does (40 images of 56x56, 1x1,
     // 320 -> 192, training pass: 149 us with 512 columns for 320, 132 with
@@ -651,7 +655,6 @@ hipError_t run_mode(IgemmBatch& b, IgemmCtl ctl, hipStream_t stream) {
     const bool big = work >= (int64_t)200 * 256 * 256 && (maxN + 255) / 256 * 256 <= (maxN + 127) / 128 * 128;
     if constexpr (MODE == kGemm || MODE == kConv) {
         if (step128) {
-            if (maxN <= 64) return launch_dma<256, 64, 2, 8, 1, 128, MODE>(b, ctl, stream);
             if (maxN <= 128) return launch_dma<128, 128, 2, 4, 2, 128, MODE>(b, ctl, stream);
             if (big) return launch_dma<256, 256, 2, 2, 4, 128, MODE>(b, ctl, stream);
             return launch_dma<128, 128, 2, 4, 2, 128, MODE>(b, ctl, stream);

@@ -89,3 +89,14 @@ def test_weight_gradient_formed_twice(case):
 def test_small_product_rows(case):
     say("small product", case)
     assert run_gemm(*case[:3]) == case[3]
+
+
+@pytest.mark.parametrize("case", [
+    (40000, 48, 1024, ["igemm_dma_main<256,64,4,8,1,64,0>"]),
+    (4096, 1100, 64, ["igemm_dma_main<128,128,4,4,2,64,0>"]),     # one step
+    (4096, 1100, 80, ["igemm_dma_main<128,128,2,4,2,128,0>"]),
+    (3072, 1100, 80, ["igemm_dma_main<128,128,4,4,2,64,0>"]),     # 216 tiles
+], ids=str)
+def test_ring_steps(case):
+    say("ring steps", case)
+    assert run_gemm(*case[:3]) == case[3]
