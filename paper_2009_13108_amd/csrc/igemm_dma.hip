@@ -152,7 +152,10 @@ __device__ __forceinline__ void epilogue_regs(v16i (&acc)[T::FN][T::FM], int8_t*
 
 // Out-of-tile accumulators are zero (their operand rows were zero-filled),
 // so including them in the maximum is harmless.  The LDS tile is written to
-// the output in 16-byte row pieces, with the backward ReLU mask applied.
+// the output in 16-byte row pieces, with the backward ReLU mask applied.  Whole
+// pieces are stored as such at any address (output rows whose channels are no
+// multiple of 16 are unaligned): byte by byte the stores alone bounded such
+// products (18508 x 1539 x 128 60.9 us, 31119 x 1165 x 128 81.7; 44.9 whole).
 template <typename T, int BM, int BN>
 __device__ __forceinline__ void store_tile(const IgemmProblem& P, int tm, int tn, const int8_t* lds) {
     constexpr int PITCH = BN + 16;
@@ -179,15 +182,14 @@ __device__ __forceinline__ void store_tile(const IgemmProblem& P, int tm, int tn
         }
         uint4 v = *(const uint4*)(lds + row * PITCH + pc * 16);
         int8_t* dst = P.out + ooff;
-        const bool full = nv == 16 && (((uintptr_t)dst) & 15) == 0;
+        const bool full = nv == 16;
         if (P.mask) {
             const int8_t* ms = P.mask + ooff;
-            uint32_t mw[4];
+            uint32_t mw[4] = {0u, 0u, 0u, 0u};
             if (full) {
-                const uint4 mv = *(const uint4*)ms;
+                const uint4 mv = load16_any(ms);
                 mw[0] = mv.x; mw[1] = mv.y; mw[2] = mv.z; mw[3] = mv.w;
             } else {
-                for (int q = 0; q < 4; q++) mw[q] = 0;
                 for (int e = 0; e < nv; e++) mw[e >> 2] |= (uint32_t)(uint8_t)ms[e] << (8 * (e & 3));
             }
             uint32_t vw[4] = {v.x, v.y, v.z, v.w};
@@ -196,7 +198,7 @@ __device__ __forceinline__ void store_tile(const IgemmProblem& P, int tm, int tn
             v = make_uint4(vw[0], vw[1], vw[2], vw[3]);
         }
         if (full) {
-            *(uint4*)dst = v;
+            store16_any(dst, v);
         } else {
             const uint32_t vw[4] = {v.x, v.y, v.z, v.w};
             for (int e = 0; e < nv; e++) dst[e] = (int8_t)(vw[e >> 2] >> (8 * (e & 3)));

@@ -207,6 +207,8 @@ __device__ __forceinline__ uint4 load16_any(const void* p) {
     return v;
 }
 
+__device__ __forceinline__ void store16_any(void* p, uint4 v) { __builtin_memcpy(p, &v, 16); }
+
 // Bytes [lo, hi) of v, zero elsewhere (0 <= lo, hi <= 16).
 __device__ __forceinline__ uint4 keep_bytes(uint4 v, int lo, int hi) {
     uint32_t w[4] = {v.x, v.y, v.z, v.w};
