@@ -305,12 +305,12 @@ __device__ __forceinline__ void dma_tile(const IgemmProblem& P, int tm, int tn, 
     int step_r = 0, step_s = 0, step_c = 0;
     uint32_t step_off = 0, row_wrap = 0;
     if constexpr (MODE == kConv16) {
-        pr = (int)kpo / P.L;
-        ps = ((int)kpo - pr * P.L) / P.C;
+        pr = div64((int)kpo, P.L);
+        ps = div64((int)kpo - pr * P.L, P.C);
         pc = (int)kpo - pr * P.L - ps * P.C;
         poff = (uint32_t)((pr * P.W + ps) * P.C + pc);
-        step_r = KS / P.L;
-        step_s = (KS - step_r * P.L) / P.C;
+        step_r = div64(KS, P.L);
+        step_s = div64(KS - step_r * P.L, P.C);
         step_c = KS - step_r * P.L - step_s * P.C;
         step_off = (uint32_t)((step_r * P.W + step_s) * P.C + step_c);
         row_wrap = (uint32_t)((P.W - P.S) * P.C);
@@ -623,6 +623,25 @@ int batch_mode(const IgemmBatch& b) {
     return mode;
 }
 
+// Carried pieces set up more per lane than the general kernel, whose 64 x 64
+// tiles also leave less of a narrow output empty.  With up to 16 output channels,
+// or a number that is no multiple of 16 (a row's last piece goes by bytes), short
+// reductions on few tiles are faster there, and with fewer than 16 channels
+// (no whole piece) not only the shortest.  Calls in us, general / ring: 507 x 36
+// x 112 13.4 / 15.1, 4096 x 20 x 288 14.3 / 15.2, 6272 x 10 x 288 9.6 / 11.1, 3724 x
+// 10 x 432 10.6 / 11.7; but 2704 x 68 x 432 16.1 / 15.5, 588 x 36 x 720 12.8 /
+// 11.4, 64 x 10 x 720 11.1 / 10.4, 83106 x 36 x 16 (652 tiles) 17.6 / 16.8, and
+// 1183 x 32 x 288 (whole pieces) 9.5 / 8.9.
+bool carried_too_short(const IgemmBatch& b) {
+    int64_t tiles128 = 0;
+    for (int i = 0; i < b.nprob; i++) {
+        const IgemmProblem& p = b.p[i];
+        if (p.Ktot > (p.Nout < 16 ? 576 : 288) || (p.Nout > 16 && p.Nout % 16 == 0)) return false;
+        tiles128 += (int64_t)((p.M + 127) / 128) * ((p.Nout + 127) / 128);
+    }
+    return tiles128 < 128;
+}
+
 template <int MODE>
 hipError_t run_mode(IgemmBatch& b, IgemmCtl ctl, hipStream_t stream) {
     int64_t work = 0;
@@ -674,7 +693,7 @@ hipError_t run_mode(IgemmBatch& b, IgemmCtl ctl, hipStream_t stream) {
 // load modes and both operands are addressable with 32-bit buffer offsets.
 bool igemm_dma_eligible(const IgemmBatch& b) {
     const int mode = batch_mode(b);
-    if (mode < 0) return false;
+    if (mode < 0 || (mode == kConv16 && carried_too_short(b))) return false;
     for (int i = 0; i < b.nprob; i++) {
         const IgemmProblem& p = b.p[i];
         if (p.act_bytes <= 0 || p.act_bytes >= ((int64_t)1 << 31) || p.wgt_bytes <= 0 ||

@@ -197,6 +197,12 @@ __device__ __forceinline__ uint32_t fdiv(uint32_t n, const FastDiv& f) {
     return (uint32_t)(((uint64_t)t + n) >> f.shift);
 }
 
+// n / d for 0 <= n <= 64 and d >= 16, without a division.
+__device__ __forceinline__ int div64(int n, int d) {
+    d = min(d, 65);
+    return (n >= d) + (n >= 2 * d) + (n >= 3 * d) + (n >= 4 * d);
+}
+
 // ---------------------------------------------------------------------------
 // 16 bytes from any address.  Global loads need no alignment on this target
 // (the compiler issues one 16-byte load), so rows at odd addresses cost one

@@ -26,7 +26,12 @@ CASES = [
     (1, 64, 14, 13, 128, 11, 11, 2, 5, oracle.PSR),  # classes of 36 and 30 taps in one launch
     (1, 16, 20, 18, 16, 16, 16, 1, 0, oracle.PSR),   # the largest filter
     (1, 16, 20, 18, 16, 17, 3, 1, 0, oracle.PSR),    # one row more: the general kernel
-    (40, 48, 28, 28, 272, 3, 3, 1, 1, oracle.PSR),   # several tiles of every kind
+    (40, 48, 28, 28, 272, 3, 3, 1, 1, oracle.PSR),   # several tiles of 128 x 128 and, back, of 256 x 64
+    (17, 80, 56, 57, 256, 1, 1, 1, 0, oracle.PSR),   # tiles of 256 x 256
+    (2, 32, 14, 14, 36, 3, 3, 1, 1, oracle.PSR),     # 288 and 324 products: short on few tiles, and not
+    (2, 16, 13, 12, 16, 3, 3, 2, 1, oracle.RTN),     # short classes of 16 channels
+    (2, 80, 14, 13, 10, 3, 3, 1, 1, oracle.PSR),     # rows without a whole piece
+    (30, 36, 28, 27, 32, 3, 3, 2, 1, oracle.PSR),    # the same on many tiles
 ]
 
 

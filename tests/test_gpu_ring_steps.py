@@ -17,7 +17,7 @@ GEMMS = [
     (4224, 1030, 16, True, oracle.PSR), (4224, 1030, 112, False, oracle.PSR), (4096, 1100, 128, True, oracle.RTN),
     (4100, 1030, 144, False, oracle.PSR), (4100, 1030, 272, True, oracle.PSR), (33000, 100, 400, True, oracle.PSR),
     (70000, 40, 208, False, oracle.PSR), (2048, 2048, 528, True, oracle.PSR), (2049, 2048, 528, True, oracle.PSR),
-    (7000, 2000, 192, False, oracle.PSR), (5200, 2700, 160, True, oracle.RTN),
+    (7000, 2000, 192, False, oracle.PSR), (5200, 2700, 160, True, oracle.RTN), (42000, 320, 144, True, oracle.PSR),
 ]
 
 

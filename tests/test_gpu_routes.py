@@ -100,3 +100,19 @@ def test_small_product_rows(case):
 def test_ring_steps(case):
     say("ring steps", case)
     assert run_gemm(*case[:3]) == case[3]
+
+
+@pytest.mark.parametrize("case", [
+    ("fwd", 1, 14, 32, 20, 3, 1, 1, "igemm_main"),        # 288 products per output, 20 channels
+    ("fwd", 1, 14, 48, 20, 3, 1, 1, "igemm_dma_main"),    # 432
+    ("fwd", 1, 14, 48, 10, 3, 1, 1, "igemm_main"),
+    ("fwd", 1, 14, 80, 10, 3, 1, 1, "igemm_dma_main"),    # 720
+    ("fwd", 1, 14, 32, 32, 3, 1, 1, "igemm_dma_main"),
+    ("bwd", 1, 32, 16, 16, 3, 2, 1, "igemm_main"),        # 16 channels
+    ("bwd", 1, 56, 36, 48, 3, 2, 1, "igemm_main"),
+    ("bwd", 60, 56, 36, 48, 3, 2, 1, "igemm_dma_main"),   # 1472 tiles
+], ids=str)
+def test_carried_pieces(case):
+    say("carried pieces", case)
+    got = run_conv(*case[:8])
+    assert len(got) == 1 and got[0].split("<")[0] == case[8], got
