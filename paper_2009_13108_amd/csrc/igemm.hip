@@ -128,7 +128,7 @@ struct Smem {
 };
 
 // One tile: accumulate, then round/store (and fold the maximum).
-template <int TBM, int TBN>
+template <int TBM, int TBN, int PF>
 __device__ __forceinline__ void run_tile(const IgemmProblem& P, int tm, int tn, Smem<TBM, TBN>& sm,
                                          const RoundK& rk, int relu, int do_store, int do_max,
                                          uint64_t& tmax) {
@@ -158,17 +158,16 @@ __device__ __forceinline__ void run_tile(const IgemmProblem& P, int tm, int tn, 
     // Loads run PF steps ahead through registers: four steps for 64 x 64
     // tiles, so that a step does not wait a memory round trip; one for larger
     // tiles, where a second would cost a wavefront per SIMD (2912 x 11248 x
-    // 624: 107 us with one, 116 with two).  LDS holds two steps, so one
-    // barrier per step is enough.
-    constexpr int PF = TBM + TBN <= 128 ? 4 : 1;
+    // 624: 107 us with one, 116 with two), and for reductions of one or two
+    // steps.  LDS holds two steps, so one barrier per step is enough.
     const int nk = (P.Ktot + BK - 1) / BK;
     uint4 ra[PF][PA], rb[PF][PB];
     // (r, j) of this thread's 16-byte piece at the next step to load, moved by
     // BK bytes per step with one carry.
-    const int lp = max(P.Lpad, 1);   // 0 for an empty reduction (no steps)
+    const int lp = max(P.Lpad, 16);   // a multiple of 16; 0 for an empty reduction (no steps)
     int kk = piece * 16;
-    int lr = kk / lp, lj = kk - lr * lp;
-    const int step_r = BK / lp, step_j = BK - step_r * lp;
+    int lr = div64(kk, lp), lj = kk - lr * lp;
+    const int step_r = div64(BK, lp), step_j = BK - step_r * lp;
     auto gload = [&](uint4 (&a)[PA], uint4 (&b)[PB]) {
 #pragma unroll
         for (int i = 0; i < PA; i++) {
@@ -310,7 +309,7 @@ __device__ __forceinline__ void run_tile(const IgemmProblem& P, int tm, int tn, 
 
 // Main launch: every tile once, maximum folded in, output rounded with the
 // shift guessed from the previous call (no output when there is no guess).
-template <int TBM, int TBN>
+template <int TBM, int TBN, int PF>
 __global__ __launch_bounds__(NTHREADS) void igemm_main(IgemmBatch batch, IgemmCtl ctl) {
     __shared__ Smem<TBM, TBN> sm;
     niti_stats* st = ctl.stats;
@@ -322,7 +321,7 @@ __global__ __launch_bounds__(NTHREADS) void igemm_main(IgemmBatch batch, IgemmCt
     RoundK rk = make_round(hint < 0 ? 0 : hint, ctl.mode);
     sr_key_current(rk, st);
     uint64_t tmax = 0;
-    run_tile<TBM, TBN>(batch.p[t.prob], t.tm, t.tn, sm, rk, ctl.relu, hint >= 0, 1, tmax);
+    run_tile<TBM, TBN, PF>(batch.p[t.prob], t.tm, t.tn, sm, rk, ctl.relu, hint >= 0, 1, tmax);
     __shared__ uint32_t red[NTHREADS / 64];
     block_publish_max32(st, slot, (uint32_t)tmax, red, snap);  // magnitudes <= 2^31
 }
@@ -331,7 +330,7 @@ __global__ __launch_bounds__(NTHREADS) void igemm_main(IgemmBatch batch, IgemmCt
 // right there is nothing to redo; otherwise every tile is recomputed and
 // rounded with the true shift.  Workgroup 0 then records the statistics and
 // the output exponent.
-template <int TBM, int TBN>
+template <int TBM, int TBN, int PF>
 __global__ __launch_bounds__(NTHREADS) void igemm_fixup(IgemmBatch batch, IgemmCtl ctl) {
     __shared__ Smem<TBM, TBN> sm;
     niti_stats* st = ctl.stats;
@@ -344,14 +343,14 @@ __global__ __launch_bounds__(NTHREADS) void igemm_fixup(IgemmBatch batch, IgemmC
         for (int tt = blockIdx.x; tt < batch.total_tiles; tt += gridDim.x) {
             const Tile t = locate_tile(batch, tt);
             uint64_t dummy = 0;
-            run_tile<TBM, TBN>(batch.p[t.prob], t.tm, t.tn, sm, rk, ctl.relu, 1, 0, dummy);
+            run_tile<TBM, TBN, PF>(batch.p[t.prob], t.tm, t.tn, sm, rk, ctl.relu, 1, 0, dummy);
             __syncthreads();
         }
     }
     if (is_finisher()) finish_call(st, ctl.target, ctl.ex, ctl.static_flags, 1);
 }
 
-template <int TBM, int TBN>
+template <int TBM, int TBN, int PF>
 hipError_t launch_igemm(IgemmBatch& b, IgemmCtl ctl, hipStream_t stream) {
     int base = 0;
     for (int i = 0; i < b.nprob; i++) {
@@ -363,14 +362,14 @@ hipError_t launch_igemm(IgemmBatch& b, IgemmCtl ctl, hipStream_t stream) {
     }
     b.total_tiles = base;
     const int tk = timing_on()
-                       ? timing_begin(NITI_TIMING_KERNEL, stream, kernel_label("igemm_main<%d,%d>", TBM, TBN))
+                       ? timing_begin(NITI_TIMING_KERNEL, stream, kernel_label("igemm_main<%d,%d,%d>", TBM, TBN, PF))
                        : -1;
-    hipLaunchKernelGGL((igemm_main<TBM, TBN>), dim3(base), dim3(NTHREADS), 0, stream, b, ctl);
+    hipLaunchKernelGGL((igemm_main<TBM, TBN, PF>), dim3(base), dim3(NTHREADS), 0, stream, b, ctl);
     timing_end(tk, stream);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     const int fix_grid = base < kFixupGrid ? base : kFixupGrid;
-    hipLaunchKernelGGL((igemm_fixup<TBM, TBN>), dim3(fix_grid), dim3(NTHREADS), 0, stream, b, ctl);
+    hipLaunchKernelGGL((igemm_fixup<TBM, TBN, PF>), dim3(fix_grid), dim3(NTHREADS), 0, stream, b, ctl);
     return hipGetLastError();
 }
 
@@ -379,11 +378,19 @@ hipError_t launch_igemm(IgemmBatch& b, IgemmCtl ctl, hipStream_t stream) {
 namespace {
 
 // 64 x 64 tiles below one 128 x 128 tile per CU: four times the workgroups,
-// and loads four steps ahead.  Measured in us at 64 / 256 / 512 as the limit:
-// 1000 x 1500 x 1111 (96 tiles of 128) 35.5 / 21.9 / 21.9; a 7x7 layer of 36
-// channels (training pass) 145 / 104 / 104; 6000 x 700 x 333 (282 tiles)
-// 29.8 / 24.5 / 31.5.
+// and loads four steps ahead.  Products in us, tiles of 128 / 64: 1000 x 1500 x
+// 1111 (96 tiles of 128) 35.5 / 21.9, 4425 x 781 x 103 (245) 25.5 / 22.4, 13999 x
+// 169 x 18 (220) 18.5 / 17.9; 6000 x 700 x 333 (282) 24.5 / 31.5.
 constexpr int64_t kSmallTiles = 256;
+// Reductions of one or two steps look ahead by one: the rest of a ring of four
+// would only be jumped over, through code not yet in the instruction cache.
+// With three or more workgroups per CU the larger ring wins, since its loads of
+// both steps go out at once.  Products in us, four ahead / one ahead: 4907 x 16
+// x 49 8.4 / 7.9, 2496 x 32 x 16 9.1 / 8.5, 1367 x 957 x 101 (88 tiles) 12.7 / 12.5,
+// 9253 x 149 x 84 (146) 14.4 / 14.1; 6336 x 509 x 26 (200) 21.4 / 23.2, 2435 x 1275
+// x 150 (200) 21.6 / 22.7.
+constexpr int kShortReduction = 128;
+constexpr int64_t kShortTiles = 160;
 
 hipError_t igemm_dispatch(IgemmBatch& b, IgemmCtl ctl, hipStream_t stream) {
     // Stochastic rounding keys each draw by the element's offset in the
@@ -393,18 +400,17 @@ hipError_t igemm_dispatch(IgemmBatch& b, IgemmCtl ctl, hipStream_t stream) {
     if (!sr && igemm_wres_eligible(b)) return igemm_wres_run(b, ctl, stream);
     if (!sr && igemm_dma_eligible(b)) return igemm_dma_run(b, ctl, stream);
     // All problems of a batch share the tile shape; pick it from the largest.
-    int maxM = 0, maxN = 0;
-    for (int i = 0; i < b.nprob; i++) {
-        maxM = b.p[i].M > maxM ? b.p[i].M : maxM;
-        maxN = b.p[i].Nout > maxN ? b.p[i].Nout : maxN;
-    }
+    int maxN = 0, maxK = 0;
     int64_t tiles128 = 0;
-    for (int i = 0; i < b.nprob; i++)
+    for (int i = 0; i < b.nprob; i++) {
+        maxN = b.p[i].Nout > maxN ? b.p[i].Nout : maxN;
+        maxK = b.p[i].Ktot > maxK ? b.p[i].Ktot : maxK;
         tiles128 += (int64_t)((b.p[i].M + 127) / 128) * ((b.p[i].Nout + 127) / 128);
-    if (tiles128 < kSmallTiles) return launch_igemm<64, 64>(b, ctl, stream);
-    (void)maxM;
-    if (maxN <= 64) return launch_igemm<256, 64>(b, ctl, stream);
-    return launch_igemm<128, 128>(b, ctl, stream);
+    }
+    if (tiles128 < kShortTiles && maxK <= kShortReduction) return launch_igemm<64, 64, 1>(b, ctl, stream);
+    if (tiles128 < kSmallTiles) return launch_igemm<64, 64, 4>(b, ctl, stream);
+    if (maxN <= 64) return launch_igemm<256, 64, 1>(b, ctl, stream);
+    return launch_igemm<128, 128, 1>(b, ctl, stream);
 }
 
 }  // namespace

@@ -116,3 +116,14 @@ def test_carried_pieces(case):
     say("carried pieces", case)
     got = run_conv(*case[:8])
     assert len(got) == 1 and got[0].split("<")[0] == case[8], got
+
+
+@pytest.mark.parametrize("case", [
+    (100, 100, 65, niti.SR, ["igemm_main<64,64,1>"]),
+    (100, 100, 200, niti.SR, ["igemm_main<64,64,4>"]),
+    (2600, 1030, 65, niti.SR, ["igemm_main<64,64,4>"]),   # 189 tiles of 128
+    (5000, 1030, 65, niti.SR, ["igemm_main<128,128,1>"]),
+], ids=str)
+def test_general_kernel_lookahead(case):
+    say("look-ahead", case)
+    assert run_gemm(*case[:4]) == case[4]
