@@ -36,6 +36,7 @@ namespace {
 
 constexpr int PIX = 64;                 // pixels per stage
 constexpr uint32_t kOOB = 0x80000000u;
+constexpr int64_t kOver = 5 * PIX;      // pixels past the last one that the ring may form offsets of, and one stage
 
 typedef __attribute__((address_space(3))) v2i lds_v2i;
 
@@ -185,8 +186,10 @@ __device__ __forceinline__ void wgrad_tile(const WgradProblem& P, int8_t* lds, i
     int next = 0;
     const uint32_t xdst = lds0 + (uint32_t)(wave * T::XPW) * 1024u;
     const uint32_t ddst = lds0 + (uint32_t)(T::XBLK + wave * T::DPW) * 1024u;
-    // kOOB offsets may move too: at most 2^31 - 1 bytes below them are valid,
-    // and a stage count times the step stays below 2^31 (wgrad_dma_eligible).
+    // kOOB offsets of channels and columns past the edge move too and may come
+    // round to the buffer: what they load is in bounds and ends in sums that
+    // are not stored.  Where all sums enter the maximum they must not
+    // (wgrad_twice_eligible).
     auto issue = [&]() {
         const uint32_t slot = (uint32_t)((next % NS) * T::STAGE);
 #pragma unroll
@@ -419,14 +422,11 @@ hipError_t launch(const WgradProblem& p, const WgradPlan& plan, hipStream_t stre
 
 bool wgrad_dma_eligible(const WgradProblem& p) {
     const bool cols = p.win ? (p.Lw % 16 == 0 && p.L % 4 == 0 && p.ph == 0 && p.pw == 0) : p.C % 16 == 0;
-    // The ring runs up to four stages past the last pixel; the offsets it
-    // forms there must not come round to the buffer again.
-    const int64_t over = 5 * PIX;
-    if (p.dy_bytes + over * p.K >= ((int64_t)1 << 31) ||
-        p.x_bytes + (over / ((int64_t)p.P * p.Q) + 2) * p.H * p.W * p.C >= ((int64_t)1 << 31))
-        return false;
+    // The ring runs up to four stages past the last pixel.  The error offsets it
+    // forms there must lie past the buffer, also mod 2^32: their zeros cancel
+    // whatever the input offsets of such pixels meet in their own buffer.
     return cols && p.K % 16 == 0 && p.x_bytes > 0 && p.x_bytes < ((int64_t)1 << 31) && p.dy_bytes > 0 &&
-           p.dy_bytes < ((int64_t)1 << 31);
+           p.dy_bytes < ((int64_t)1 << 31) && p.dy_bytes + kOver * p.K < ((int64_t)1 << 32);
 }
 
 hipError_t wgrad_dma_run(WgradProblem& p, const WgradPlan& plan, hipStream_t stream) {
@@ -450,6 +450,8 @@ hipError_t wgrad_dma_run(WgradProblem& p, const WgradPlan& plan, hipStream_t str
 // pixels 14.8 / 16.0.
 bool wgrad_twice_eligible(const WgradProblem& p, const WgradPlan& plan, int mode) {
     if (plan.splits != 1 || p.win || p.npix > 512 || p.K <= 32 || !wgrad_dma_eligible(p)) return false;
+    const int64_t edge = p.K > p.C ? p.K : p.C;   // offsets past the edge stay past the buffers
+    if ((p.npix + kOver) * edge >= ((int64_t)1 << 31)) return false;
     const int64_t weights = (int64_t)p.K * p.ncol;
     return mode == NITI_ROUND_SR ? weights >= (1 << 17) + (int64_t)2048 * p.npix
                                  : weights >= (1 << 15) + (int64_t)512 * p.npix;

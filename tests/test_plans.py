@@ -33,3 +33,10 @@ def test_nine_run_weight_gradient_fills_one_round(c, k, h, stride, pad):
         assert got == low or tiles * got <= 256, n
         if got > low:
             assert -(-stages // got) >= 13, n
+
+
+def test_near_two_gigabytes_keeps_the_lds_kernel():
+    """Operands whose size is just below 2 GiB: the plan of the LDS-staged
+    kernel (ranges for three workgroups per CU), as for smaller ones."""
+    d = niti.ConvDesc.make(1, (1 << 27) - 1, 1, 16, 16, 1, 1, 1, 0)
+    assert splits(d) == 768
