@@ -410,7 +410,7 @@ hipError_t launch(const WgradProblem& p, const WgradPlan& plan, hipStream_t stre
     // per CU and no more.
     if (EP != kStore && grid > 512) grid = 512;
     const int t = timing_on() ? timing_begin(NITI_TIMING_KERNEL, stream,
-                                             kernel_label("wgrad_dma_kernel<%d,%d,%d>", TBK, TBC, NS))
+                                             kernel_label("wgrad_dma_kernel<%d,%d,%d,%d>", TBK, TBC, NS, EP))
                               : -1;
     hipLaunchKernelGGL((wgrad_dma_kernel<TBK, TBC, NS, EP>), dim3((unsigned)grid), dim3(256), T::LDS, stream, p, tc, tk,
                        plan.splits, fin);

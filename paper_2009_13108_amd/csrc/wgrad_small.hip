@@ -131,14 +131,13 @@ hipError_t wgrad_small_run(WgradProblem& p, int8_t* w, int32_t* g32, int mu, int
                            uint32_t static_flags, hipStream_t stream) {
     p.part = g32;
     const int tc = (p.C + 31) / 32, tk = (p.K + 31) / 32;
-    const char* label = timing_on() ? kernel_label("wgrad_small_kernel") : nullptr;
-    int t = label ? timing_begin(NITI_TIMING_KERNEL, stream, label) : -1;
+    int t = timing_on() ? timing_begin(NITI_TIMING_KERNEL, stream, kernel_label("wgrad_small_kernel<%d>", -1)) : -1;
     const dim3 grid(tc * tk), block(ST);
     hipLaunchKernelGGL(wgrad_small_kernel<-1>, grid, block, 0, stream, p, w, st, mu, static_flags, tc);
     timing_end(t, stream);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    t = label ? timing_begin(NITI_TIMING_KERNEL, stream, label) : -1;
+    t = timing_on() ? timing_begin(NITI_TIMING_KERNEL, stream, kernel_label("wgrad_small_kernel<%d>", mode)) : -1;
     if (mode == NITI_ROUND_SR)
         hipLaunchKernelGGL(wgrad_small_kernel<NITI_ROUND_SR>, grid, block, 0, stream, p, w, st, mu, static_flags, tc);
     else if (mode == NITI_ROUND_RTN)

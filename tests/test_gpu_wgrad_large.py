@@ -52,4 +52,4 @@ def test_just_below_two_gigabytes(case, sparse):
     assert (host(g32).reshape(k, c) == exp).all()
     assert niti.read_stats(stats)[0]["max_abs"] == np.abs(exp).max()
     assert [name for _, name, _ in niti.timing_records() if name.startswith("wgrad")] == [
-        "wgrad_dma_kernel<%d,128,4>" % (64 if k <= 64 else 128)]
+        "wgrad_dma_kernel<%d,128,4,-2>" % (64 if k <= 64 else 128)]
