@@ -1,10 +1,11 @@
-"""Nine-tap weight gradients with shared rows (3x3, stride 1, padding 1) at the
-edges of the scheme: images one row or one or two columns wide, where every
-pixel is on a border; rows shorter and longer than the 16 pixels of a lane and
-the 128 of a stage; images smaller than a stage, so that one stage holds
-several; pixel counts that end inside a stage; several ranges.  The strided and
-unpadded layers beside them keep the nine separate runs.  Exact against the
-oracle."""
+"""Nine-tap weight gradients with shared rows (3x3, stride 1, padding 1, at
+least 128 input channels) at the edges of the scheme: images one row or one or
+two columns wide, where every pixel is on a border; rows shorter and longer
+than the 16 pixels of a lane and the 128 of a stage; images smaller than a
+stage, so that one stage holds several; pixel counts that end inside a stage;
+several ranges, with borders inside an image row.  Layers of 64 channels and
+the strided and unpadded ones beside them keep the nine separate runs.  The
+kernel that ran is read from the timing records.  Exact against the oracle."""
 import pytest
 
 import oracle
@@ -14,17 +15,27 @@ from helpers import dev, host, kcrs, krsc, nhwc, same_stats, say
 
 pytestmark = pytest.mark.gpu
 
-CASES = [
+SHARED = [
     # n, c, h, w, k, stride, pad
+    (3, 128, 1, 1, 64, 1, 1), (5, 128, 1, 40, 64, 1, 1), (7, 192, 33, 1, 64, 1, 1), (9, 128, 5, 2, 128, 1, 1),
+    (300, 128, 1, 1, 64, 1, 1), (40, 128, 7, 7, 64, 1, 1), (11, 128, 3, 15, 64, 1, 1), (11, 192, 3, 16, 64, 1, 1),
+    (11, 128, 3, 17, 64, 1, 1), (4, 128, 9, 17, 192, 1, 1), (2, 128, 4, 127, 64, 1, 1), (2, 128, 4, 128, 64, 1, 1),
+    (2, 128, 4, 130, 64, 1, 1), (2, 192, 3, 300, 64, 1, 1), (1, 128, 128, 129, 64, 1, 1), (30, 192, 14, 15, 128, 1, 1),
+    (1, 128, 60, 60, 64, 1, 1),     # ranges of 384 pixels, which end inside rows of 60
+    (70, 256, 7, 7, 128, 1, 1),     # ranges that end inside images of 49
+    (1, 128, 2, 1, 64, 1, 1), (2, 128, 2, 2, 64, 1, 1),
+]
+NINE = [
     (3, 64, 1, 1, 64, 1, 1), (5, 64, 1, 40, 64, 1, 1), (7, 64, 33, 1, 64, 1, 1), (9, 64, 5, 2, 128, 1, 1),
-    (40, 128, 7, 7, 64, 1, 1), (11, 64, 3, 16, 64, 1, 1), (4, 64, 9, 17, 192, 1, 1), (2, 64, 4, 130, 64, 1, 1),
-    (2, 64, 3, 300, 64, 1, 1), (1, 64, 128, 129, 64, 1, 1), (30, 192, 14, 15, 128, 1, 1),
-    (3, 64, 9, 9, 64, 1, 0), (3, 64, 9, 9, 64, 2, 1), (2, 64, 8, 8, 64, 1, 2),
+    (4, 64, 9, 17, 192, 1, 1), (2, 64, 4, 130, 64, 1, 1), (1, 64, 128, 129, 64, 1, 1),
+    (3, 128, 9, 9, 64, 1, 0), (3, 128, 9, 9, 64, 2, 1), (2, 64, 8, 8, 64, 1, 2), (3, 64, 9, 9, 64, 1, 0),
+    (3, 64, 9, 9, 64, 2, 1),
 ]
 
 
-@pytest.mark.parametrize("case", CASES)
-def test_shared_rows(case):
+@pytest.mark.parametrize("case, kernel", [(c, "wgrad_tap_kernel<5,1>") for c in SHARED] +
+                         [(c, "wgrad_tap_kernel<3,0>") for c in NINE])
+def test_shared_rows(case, kernel):
     import torch
     n, c, h, w, k, stride, pad = case
     say("shared rows", case)
@@ -37,6 +48,10 @@ def test_shared_rows(case):
     g32 = torch.empty(gd.w_shape(), dtype=torch.int32, device="cuda")
     stats = niti.new_stats()
     wd = dev(krsc(wt))
-    niti.conv_bwd_weight(gd, dev(nhwc(x)), dev(nhwc(dy)), wd, stats, ws, g32_out=g32, mu=5)
+    xd, dyd = dev(nhwc(x)), dev(nhwc(dy))
+    niti.timing_enable(True)
+    niti.conv_bwd_weight(gd, xd, dyd, wd, stats, ws, g32_out=g32, mu=5)
+    niti.timing_enable(False)
     assert (kcrs(host(g32)) == exp_g).all()
     assert (kcrs(host(wd)) == exp_w).all() and same_stats(niti.read_stats(stats)[0], st)
+    assert [name for fam, name, _ in niti.timing_records() if fam == niti.TIMING_KERNEL] == [kernel]
