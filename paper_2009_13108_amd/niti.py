@@ -37,7 +37,8 @@ STATS_DTYPE = np.dtype([
     ("max_abs", "<u8"), ("b", "<i4"), ("bp", "<i4"), ("flags", "<i4"), ("s_out", "<i4"),
     ("bp_hint", "<i4"), ("calls", "<u4"), ("misses", "<u4"), ("reserved0", "<u4"),
     ("acc_max", "<u8", (2,)), ("wflags", "<u4", (2,)), ("cur", "<i4"), ("hint_used", "<i4"),
-    ("sr_seed", "<u8"), ("sr_call", "<u4"), ("reserved", "<u4", (11,)),
+    ("sr_seed", "<u8"), ("sr_call", "<u4"), ("level", "<i4"), ("trust", "<i4"),
+    ("reserved", "<u4", (9,)),
 ])
 assert STATS_DTYPE.itemsize == STATS_BYTES
 

@@ -1,7 +1,9 @@
-"""The speculated shift follows the maximum's running level: results are the
-oracle's whatever the guess, and on constant inputs the guess settles, from
-above and from below, from one octave away and from many, also where the
-maximum is a power of two or one below it."""
+"""The speculated shift is the last call's, or that of the maximum's running
+level where that has been right more often.  Results are the oracle's whatever
+the guess; on constant inputs the guess settles, from above and from below, from
+one octave away and from many, also where the maximum is a power of two or one
+below it; and the level is chosen where single calls leave its octave, the last
+call where the maximum drifts."""
 import numpy as np
 import pytest
 
@@ -41,3 +43,46 @@ def test_guess_settles_on_constant_inputs(tops):
             if call == 11:
                 settled = niti.read_stats(stats)[0]["misses"]
         assert niti.read_stats(stats)[0]["misses"] == settled, top
+
+
+def expected(maxima, target=7):
+    """(level, trust, bp, hint, misses) after each call, from the rule's own
+    terms: the level is the bitwidth and the fraction below its leading bit, in
+    256ths (maxima below 2^24, which float32 holds exactly)."""
+    level = trust = bp = hint = misses = 0
+    rows = []
+    for mx in maxima:
+        b = int(mx).bit_length()
+        now = max(b - target, 0)
+        misses += hint != now
+        lv = (max(b, 1) << 8) + ((max(mx, 1) << 8 >> max(b - 1, 0)) & 255)
+        was = max((level >> 8) - target, 0)
+        trust = min(max(trust + (was == now) - (bp == now), -3), 3)
+        d = lv - level
+        level = lv if abs(d) >= 384 else level + ((d + 3 * (d > 0)) >> 2)
+        bp = now
+        hint = max((level >> 8) - target, 0) if trust > 0 else bp
+        rows.append((level, trust, bp, hint, misses))
+    return rows
+
+
+@pytest.mark.parametrize("maxima,chosen", [([8300, 8100, 8400] * 6, True), ([8150, 8200, 7900, 8000] * 5, True),
+                                           ([100 << (i // 2) for i in range(14)], False),
+                                           ([5000, 0, 5000, 1, 0, 70000, 2, 3], False)])
+def test_guess_follows_the_better_of_level_and_last_call(maxima, chosen):
+    import torch
+    say("guess", maxima[:4])
+    K = 8192
+    Bd = dev(np.ones((8, K), np.int8))
+    C = torch.empty((4, 8), dtype=torch.int8, device="cuda")
+    stats = niti.new_stats()
+    rows = expected(maxima)
+    assert any(hint != bp for _, _, bp, hint, _ in rows) == chosen
+    for call, mx in enumerate(maxima):
+        A = np.zeros((4, K), np.int8)
+        A[2, :mx // 127] = 127
+        A[2, mx // 127] = mx % 127
+        niti.gemm_fwd(dev(A), Bd, C, stats)
+        got = niti.read_stats(stats)[0]
+        assert got["max_abs"] == mx
+        assert tuple(got[f] for f in ("level", "trust", "bp", "bp_hint", "misses")) == rows[call], (call, got)
