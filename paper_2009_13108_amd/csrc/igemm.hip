@@ -308,7 +308,7 @@ __device__ __forceinline__ void run_tile(const IgemmProblem& P, int tm, int tn, 
 }
 
 // Main launch: every tile once, maximum folded in, output rounded with the
-// shift guessed from the previous call (no output when there is no guess).
+// guessed shift (no output when there is no guess).
 template <int TBM, int TBN, int PF>
 __global__ __launch_bounds__(NTHREADS) void igemm_main(IgemmBatch batch, IgemmCtl ctl) {
     __shared__ Smem<TBM, TBN> sm;

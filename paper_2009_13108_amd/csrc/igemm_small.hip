@@ -14,9 +14,9 @@
 // 64 consecutive bytes of 16 rows; the 32 x 32 x 32 one read 32 of 32 rows, and
 // rows are far apart, so that each instruction touched twice as many cache
 // lines for the same data.  The epilogue (optional ReLU, tensor maximum, shift-and-round,
-// backward ReLU mask) and the exponent handling (rounding with the previous
-// call's shift, then a fix-up launch that recomputes on a miss) are those of
-// the other implicit-GEMM kernels.
+// backward ReLU mask) and the exponent handling (rounding with a guessed
+// shift, then a fix-up launch that recomputes on a miss) are those of the
+// other implicit-GEMM kernels.
 #include "niti_internal.h"
 
 namespace niti {
@@ -164,7 +164,7 @@ __device__ __forceinline__ void small_tile(const IgemmProblem& P, int tile, int3
 }
 
 // Main launch: every tile once, the maximum folded in, the output rounded
-// with the shift of the previous call (none stored without a guess).
+// with a guessed shift (none stored without one).
 template <bool WHOLE, int FM>
 __global__ __launch_bounds__(ST) void igemm_small_main(IgemmProblem P, IgemmCtl ctl) {
     __shared__ __attribute__((aligned(16))) int32_t red[SW * 16 * FM * RP];

@@ -11,8 +11,8 @@
 // same time, so they meet in L2 instead of re-reading memory past it, which
 // is what bounds a kernel that tiles the im2col columns independently.
 //
-// The pixel reduction is split over about one workgroup per CU and every
-// workgroup writes its partial tile, which the split-sum pass reads back:
+// The pixel reduction is split over three quarters to one workgroup per CU
+// (wgrad_tap_plan) and every workgroup writes its partial tile, which the split-sum pass reads back:
 // that traffic is the workgroup count times the tile size.  A 32-channel
 // chunk halves it against a 64-channel one, for 10% more operand loads per
 // multiply-add (the error slice is shared by fewer taps' columns).
