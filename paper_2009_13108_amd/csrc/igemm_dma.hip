@@ -642,29 +642,54 @@ bool carried_too_short(const IgemmBatch& b) {
     return tiles128 < 128;
 }
 
+// K steps of 128 bytes per row, or of 64 in a ring of twice the stages.  Called
+// where a step is uniform (matrix rows, or channels in whole 128s; windows and
+// carried pieces stay at 64: 5x5, 96 channels, training pass 272 us at 64, 287
+// at 128) and tiles are wider than 64 columns (256 x 64 tiles gain nothing from
+// the longer rows and lose the ring's depth: 50176 x 64 x 3456 27.9 / 31.1).
+// They pay where whole cache lines are loaded many times over: 14x14, 256
+// channels, batch 128 (training pass) 104.0 / 97.7; 8192^3 421 / 404.  They lose
+//  - up to one 128 x 128 tile per CU (2048^3 18.8 / 19.5);
+//  - where a reduction ends with 64 bytes or fewer in its last step, which is
+//    then half empty, unless it is long;
+//  - in 256 x 256 tiles where rows are odd multiples of 64 bytes: every other
+//    row's pieces then straddle two lines, which 64-byte ones never do;
+//  - in short reductions, the sooner the more rounds of tiles there are (two
+//    workgroups share a CU, 512 tiles a round).
+// Products in us at 64 / 128: 2009 x 3664 x 8592 132.4 / 96.4, 6115 x 1712 x 13472
+// 255.0 / 229.5; but 12760 x 3952 x 448 52.0 / 58.7 (half a step), 17657 x 8592 x
+// 192 103.5 / 111.8 (256 x 256 tiles, odd multiple of 64), 14995 x 15456 x 512
+// 218.9 / 241.4 (short, 14000 tiles), 1815 x 4811 x 1728 33.5 / 38.4 (570 tiles).
+// The limits are from 7000 random products timed both ways: of those with 128
+// wherever there is more than one tile per CU 18% were more than 3% slower than
+// the better form, with these limits 5%; 1x1 layers of 128 to 512 channels on
+// 256 x 256 tiles are 2 to 6% faster.
+constexpr int kHalfStep = 64;
+bool wide_steps(int K, int64_t tiles128, bool big) {
+    const int tail = K % 128;   // bytes in the last step (0: a whole one)
+    const bool half_empty = tail != 0 && tail <= kHalfStep;
+    if (tiles128 <= 256) return false;
+    if (big) return tail != kHalfStep && K >= (half_empty ? 2048 : 640);
+    if (tiles128 > 1536) return K >= (half_empty ? 1536 : 768);
+    // A last round that leaves most CUs one workgroup hides less behind the
+    // shallow ring; with misaligned rows as well the deep one wins.
+    if (tail == kHalfStep && (tiles128 - 1) % 512 < 256 && K >= 1024 && K < 4096) return false;
+    return K >= 384;
+}
+
 template <int MODE>
 hipError_t run_mode(IgemmBatch& b, IgemmCtl ctl, hipStream_t stream) {
     int64_t work = 0;
-    int maxN = 0;
+    int maxN = 0, maxK = 0;
     int64_t tiles128 = 0;
+    bool whole128 = true;   // kConv: every step of 128 bytes lies in one tap
     for (int i = 0; i < b.nprob; i++) {
         work += (int64_t)b.p[i].M * b.p[i].Nout;
         maxN = b.p[i].Nout > maxN ? b.p[i].Nout : maxN;
+        maxK = b.p[i].Ktot > maxK ? b.p[i].Ktot : maxK;
+        whole128 = whole128 && b.p[i].C % 128 == 0;
         tiles128 += (int64_t)((b.p[i].M + 127) / 128) * ((b.p[i].Nout + 127) / 128);
     }
-    // K steps of 128 bytes where a step is uniform (rows, or channels in whole
-    // 128s), the reduction is more than one step of 64 and there is more than
-    // one 128 x 128 tile per CU; windows and carried pieces stay at 64.
-    // Measured in us at 64 / 128: 14x14, 256 channels, batch 128 (training pass)
-    // 104.0 / 97.7; 8192^3 421 / 404; 4096^3 63.3 / 61.3; but 7x7, 512 channels
-    // (196 tiles, one per CU and a deep ring either way) 97.1 / 97.1, 2048^3
-    // 18.8 / 19.5, and 5x5, 96 channels (carried pieces) 272 / 287.  One step:
-    // 16930 x 192 x 64 9.9 / 10.7.  Tiles of 64 columns gain nothing from the
-    // longer rows and lose the ring's depth (four stages against two): 50176 x
-    // 64 x 3456 27.9 / 31.1, x 2304 23.3 / 25.7, 35105 x 42 x 1024 15.4 / 16.4.
-    bool step128 = (MODE == kGemm || MODE == kConv) && maxN > 64 && tiles128 > 256;
-    for (int i = 0; i < b.nprob; i++)
-        step128 = step128 && b.p[i].Ktot > 64 && (MODE != kConv || b.p[i].C % 128 == 0);
     // 256 x 256 tiles where they give most compute units a workgroup and pad
     // the channels no further than 128 does (40 images of 56x56, 1x1,
     // 320 -> 192, training pass: 149 us with 512 columns for 320, 132 with
@@ -674,6 +699,7 @@ hipError_t run_mode(IgemmBatch& b, IgemmCtl ctl, hipStream_t stream) {
     // SIMD, took the same or longer everywhere: 3000 x 3000 x 256 35.5 us
     // against 25.6, 28x28 192 -> 160 training pass 157 against 126).
     const bool big = work >= (int64_t)200 * 256 * 256 && (maxN + 255) / 256 * 256 <= (maxN + 127) / 128 * 128;
+    const bool step128 = (MODE == kGemm || (MODE == kConv && whole128)) && maxN > 64 && wide_steps(maxK, tiles128, big);
     if constexpr (MODE == kGemm || MODE == kConv) {
         if (step128) {
             if (maxN <= 128) return launch_dma<128, 128, 2, 4, 2, 128, MODE>(b, ctl, stream);

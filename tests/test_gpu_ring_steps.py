@@ -18,6 +18,10 @@ GEMMS = [
     (4100, 1030, 144, False, oracle.PSR), (4100, 1030, 272, True, oracle.PSR), (33000, 100, 400, True, oracle.PSR),
     (70000, 40, 208, False, oracle.PSR), (2048, 2048, 528, True, oracle.PSR), (2049, 2048, 528, True, oracle.PSR),
     (7000, 2000, 192, False, oracle.PSR), (5200, 2700, 160, True, oracle.RTN), (42000, 320, 144, True, oracle.PSR),
+    # steps of 128 bytes: whole ones, and last ones of 16, 64, 80 and 112; then in tiles of 256
+    (4224, 1030, 384, True, oracle.PSR), (4100, 1030, 400, False, oracle.PSR), (4100, 1030, 576, True, oracle.RTN),
+    (4100, 1030, 464, False, oracle.PSR), (4100, 1030, 496, True, oracle.PSR), (13200, 1000, 640, False, oracle.PSR),
+    (13200, 1000, 720, True, oracle.PSR),
 ]
 
 

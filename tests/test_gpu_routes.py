@@ -92,14 +92,39 @@ def test_small_product_rows(case):
 
 
 @pytest.mark.parametrize("case", [
-    (40000, 48, 1024, ["igemm_dma_main<256,64,4,8,1,64,0>"]),
-    (4096, 1100, 64, ["igemm_dma_main<128,128,4,4,2,64,0>"]),     # one step
-    (4096, 1100, 80, ["igemm_dma_main<128,128,2,4,2,128,0>"]),
-    (3072, 1100, 80, ["igemm_dma_main<128,128,4,4,2,64,0>"]),     # 216 tiles
+    (40000, 48, 1024, "256,64,4,8,1,64"),
+    (4096, 1100, 64, "128,128,4,4,2,64"),        # 288 tiles: one step,
+    (4096, 1100, 368, "128,128,4,4,2,64"),       # a short reduction,
+    (4096, 1100, 384, "128,128,2,4,2,128"),
+    (4096, 1100, 1088, "128,128,2,4,2,128"),
+    (3072, 1100, 1152, "128,128,4,4,2,64"),      # 216 tiles
+    (4096, 2176, 1088, "128,128,4,4,2,64"),      # 544: the second round leaves most CUs one; odd multiple of 64
+    (4096, 2176, 1152, "128,128,2,4,2,128"),
+    (16384, 1664, 752, "128,128,4,4,2,64"),      # 1664 tiles
+    (16384, 1664, 768, "128,128,2,4,2,128"),
+    (16384, 1664, 1072, "128,128,4,4,2,64"),     # the last step is half empty
+    (16384, 1664, 1584, "128,128,2,4,2,128"),
+    (16384, 1024, 624, "256,256,3,2,4,64"),      # tiles of 256
+    (16384, 1024, 640, "256,256,2,2,4,128"),
+    (16384, 1024, 1072, "256,256,3,2,4,64"),
+    (16384, 1024, 2096, "256,256,2,2,4,128"),
+    (16384, 1024, 2112, "256,256,3,2,4,64"),     # odd multiple of 64
 ], ids=str)
 def test_ring_steps(case):
     say("ring steps", case)
-    assert run_gemm(*case[:3]) == case[3]
+    assert run_gemm(*case[:3]) == ["igemm_dma_main<%s,0>" % case[3]]
+
+
+@pytest.mark.parametrize("case", [
+    ("fwd", 60, 28, 128, 256, 1, 1, 0, "128,128,4,4,2,64"),     # 368 x 2 tiles, 128 products per output
+    ("fwd", 60, 28, 128, 160, 3, 1, 1, "128,128,2,4,2,128"),
+    ("fwd", 80, 28, 512, 256, 1, 1, 0, "256,256,3,2,4,64"),
+    ("fwd", 80, 28, 640, 256, 1, 1, 0, "256,256,2,2,4,128"),
+    ("fwd", 60, 28, 192, 160, 3, 1, 1, "128,128,4,4,2,64"),     # channels that are not whole 128s
+], ids=str)
+def test_ring_steps_of_convolutions(case):
+    say("ring steps", case)
+    assert run_conv(*case[:8]) == ["igemm_dma_main<%s,1>" % case[8]]
 
 
 @pytest.mark.parametrize("case", [
