@@ -232,16 +232,24 @@ hipError_t launch_small(const IgemmProblem& p, const IgemmCtl& ctl, hipStream_t 
 }  // namespace
 
 // 64 rows per tile read the weights half as often; taken where tiles of 32
-// rows are more than one per CU, so that a second round of them would follow.
+// rows are more than one per CU, so that a second round of them would follow,
+// and those of 64 are not, or the reduction is one batch of their loads (2048
+// bytes; half of that where pieces are unaligned): tiles of 64 rows that are a
+// round and a little more, each of several memory round trips, lose to
+// those of 32, of which two share a CU.
 // Products in us, tiles of 32 / 64 rows: 64 x 4096 x 4096 (256 tiles of 32)
 // 15.3 / 17.5, 63 x 2645 x 4192 (166) 12.3 / 13.8; 67 x 2765 x 200 (261) 10.7 /
 // 8.4, 353 x 1084 x 2588 (408) 20.2 / 13.1, 44 x 6541 x 1844 (410) 19.6 / 12.5.
+// 89 x 4688 x 2880 (441 of 32, 294 of 64) 14.8 / 19.3, 1003 x 655 x 3280 (672,
+// 336) 21.2 / 27.5, 195 x 3328 x 2058 (728, 416) 27.8 / 36.7.
 // Training passes at batch 128, 32 rows / 64 rows: 4096 -> 4096 84.6 / 76.2;
 // 9216 -> 4096 138.5 / 130.4; 4096 -> 1000 87.0 / 78.4.
 hipError_t igemm_small_run(IgemmBatch& b, IgemmCtl ctl, hipStream_t stream) {
     const IgemmProblem& p = b.p[0];
-    const bool tall = p.M > 32 && (int64_t)((p.M + 31) / 32) * ((p.Nout + 31) / 32) > 256;
-    if (p.L % 16 == 0) return tall ? launch_small<true, 4>(p, ctl, stream) : launch_small<true, 2>(p, ctl, stream);
+    const int64_t cols = (p.Nout + 31) / 32, low = (p.M + 31) / 32 * cols, high = (p.M + 63) / 64 * cols;
+    const bool whole = p.L % 16 == 0;
+    const bool tall = p.M > 32 && low > 256 && (high <= 256 || p.L <= (whole ? 2048 : 1024));
+    if (whole) return tall ? launch_small<true, 4>(p, ctl, stream) : launch_small<true, 2>(p, ctl, stream);
     return tall ? launch_small<false, 4>(p, ctl, stream) : launch_small<false, 2>(p, ctl, stream);
 }
 

@@ -85,6 +85,11 @@ def test_weight_gradient_formed_twice(case):
     (33, 4128, 256, ["igemm_small_main<1,4>"]),            # 258
     (44, 6541, 1844, ["igemm_small_main<0,4>"]),
     (32, 8000, 256, ["igemm_small_main<1,2>"]),            # no second 32 rows
+    (84, 4688, 2048, ["igemm_small_main<1,4>"]),           # 441 of 32 rows, 294 of 64: one batch of loads,
+    (84, 4688, 2064, ["igemm_small_main<1,2>"]),           # and more
+    (84, 4688, 1023, ["igemm_small_main<0,4>"]),
+    (84, 4688, 1025, ["igemm_small_main<0,2>"]),
+    (84, 4096, 4096, ["igemm_small_main<1,4>"]),           # 256 of 64 rows
 ], ids=str)
 def test_small_product_rows(case):
     say("small product", case)
