@@ -654,12 +654,11 @@ bool carried_too_short(const IgemmBatch& b) {
 //    then half empty, unless it is long;
 //  - in 256 x 256 tiles where rows are odd multiples of 64 bytes: every other
 //    row's pieces then straddle two lines, which 64-byte ones never do;
-//  - in short reductions, the sooner the more rounds of tiles there are (two
-//    workgroups share a CU, 512 tiles a round).
-// Products in us at 64 / 128: 2009 x 3664 x 8592 132.4 / 96.4, 6115 x 1712 x 13472
-// 255.0 / 229.5; but 12760 x 3952 x 448 52.0 / 58.7 (half a step), 17657 x 8592 x
-// 192 103.5 / 111.8 (256 x 256 tiles, odd multiple of 64), 14995 x 15456 x 512
-// 218.9 / 241.4 (short, 14000 tiles), 1815 x 4811 x 1728 33.5 / 38.4 (570 tiles).
+//  - in short reductions, the sooner the more rounds of tiles there are.
+// Products in us at 64 / 128: 2009 x 3664 x 8592 132.4 / 96.4, 1163 x 15776 x 8192
+// (256 x 256 tiles) 213.3 / 184.0; but 12760 x 3952 x 448 52.0 / 58.7 and 8660 x
+// 12508 x 304 (256) 101.8 / 109.1 (half a step), 15524 x 944 x 11328 (256) 153.7 /
+// 168.4 and 1815 x 4811 x 1728 (570 tiles) 33.5 / 38.4 (odd multiples of 64).
 // The limits are from 7000 random products timed both ways: of those with 128
 // wherever there is more than one tile per CU 18% were more than 3% slower than
 // the better form, with these limits 5%; 1x1 layers of 128 to 512 channels on
@@ -677,6 +676,26 @@ bool wide_steps(int K, int64_t tiles128, bool big) {
     return K >= 384;
 }
 
+// 256 x 256 tiles, one per CU, or 128 x 128 with eight 32 x 64 waves: two
+// workgroups per CU and four waves per SIMD, which hide each other's LDS and
+// barrier waits (256 x 128 tiles, one wave per SIMD, were slower: 3000 x 3000 x
+// 256 35.5 us against 25.6, 28x28 192 -> 160 training pass 157 against 126).
+// Which are faster goes by rounds, 256 tiles or 512: by how far each overfills
+// its last one and pads the edges.  A round of 128 covers half the area of one
+// of 256 and takes about 1.7 K + 4000 where half the latter takes K + 4000.
+// Products in us, tiles of 128 / 256 (rounds): 2321 x 5958 x 12352 231.7 / 154.8
+// (2, 1), 2819 x 10544 x 1136 73.9 / 53.6 (4, 2); but 3108 x 5008 x 9600 144.3 /
+// 206.4 (2, 2), 7235 x 6880 x 384 49.4 / 66.3 (7, 4).  Over 8400 random products
+// and convolutions the choice takes 1.4% longer than the better one; 256
+// wherever it does not pad the channels further than 128 took 6.3%.
+bool tiles_of_256(const IgemmBatch& b, int64_t K, int64_t tiles128) {
+    int64_t tiles256 = 0;
+    for (int i = 0; i < b.nprob; i++)
+        tiles256 += (int64_t)((b.p[i].M + 255) / 256) * ((b.p[i].Nout + 255) / 256);
+    const int64_t r256 = (tiles256 + 255) / 256, r128 = (tiles128 + 511) / 512;
+    return 20 * r256 * (K + 4000) <= r128 * (17 * K + 40000);
+}
+
 template <int MODE>
 hipError_t run_mode(IgemmBatch& b, IgemmCtl ctl, hipStream_t stream) {
     int64_t work = 0;
@@ -690,15 +709,7 @@ hipError_t run_mode(IgemmBatch& b, IgemmCtl ctl, hipStream_t stream) {
         whole128 = whole128 && b.p[i].C % 128 == 0;
         tiles128 += (int64_t)((b.p[i].M + 127) / 128) * ((b.p[i].Nout + 127) / 128);
     }
-    // 256 x 256 tiles where they give most compute units a workgroup and pad
-    // the channels no further than 128 does (40 images of 56x56, 1x1,
-    // 320 -> 192, training pass: 149 us with 512 columns for 320, 132 with
-    // 384); 8192^3 480 us in tiles of 128, 402 in these.  Otherwise 128 x 128
-    // with eight 32 x 64 waves: two workgroups per CU and four waves per SIMD
-    // hide each other's LDS and barrier waits (256 x 128 tiles, one wave per
-    // SIMD, took the same or longer everywhere: 3000 x 3000 x 256 35.5 us
-    // against 25.6, 28x28 192 -> 160 training pass 157 against 126).
-    const bool big = work >= (int64_t)200 * 256 * 256 && (maxN + 255) / 256 * 256 <= (maxN + 127) / 128 * 128;
+    const bool big = maxN > 128 && work >= (int64_t)200 * 256 * 256 && tiles_of_256(b, maxK, tiles128);
     const bool step128 = (MODE == kGemm || (MODE == kConv && whole128)) && maxN > 64 && wide_steps(maxK, tiles128, big);
     if constexpr (MODE == kGemm || MODE == kConv) {
         if (step128) {

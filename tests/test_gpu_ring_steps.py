@@ -2,7 +2,7 @@
 oracle: reductions that end inside a 64- and a 128-byte step, one step, one
 more than the ring holds; channels in whole 128s, whole 64s and both in one
 layer's two directions; tile counts on both sides of one tile per CU; output
-channels that 256-column tiles would pad further than 128-column ones."""
+channels that 256-column tiles pad further than 128-column ones, in either."""
 import pytest
 
 import oracle
@@ -21,7 +21,7 @@ GEMMS = [
     # steps of 128 bytes: whole ones, and last ones of 16, 64, 80 and 112; then in tiles of 256
     (4224, 1030, 384, True, oracle.PSR), (4100, 1030, 400, False, oracle.PSR), (4100, 1030, 576, True, oracle.RTN),
     (4100, 1030, 464, False, oracle.PSR), (4100, 1030, 496, True, oracle.PSR), (13200, 1000, 640, False, oracle.PSR),
-    (13200, 1000, 720, True, oracle.PSR),
+    (13200, 1000, 720, True, oracle.PSR), (12800, 1100, 144, False, oracle.RTN),
 ]
 
 
