@@ -654,7 +654,12 @@ bool carried_too_short(const IgemmBatch& b) {
 //    then half empty, unless it is long;
 //  - in 256 x 256 tiles where rows are odd multiples of 64 bytes: every other
 //    row's pieces then straddle two lines, which 64-byte ones never do;
-//  - in short reductions, the sooner the more rounds of tiles there are.
+//  - in short reductions, the sooner the more rounds of tiles there are;
+//  - where less than half the CUs have two workgroups, or the last round leaves
+//    most of them one: the ring is then all that hides a load.  Above all in
+//    convolutions, whose rows are gathered tap by tap (3x3 on 525 tiles, 22320 x
+//    320 x 2304 33.0 / 44.9; on 360, 23004 x 256 x 1152 18.0 / 21.2; but on 392,
+//    28x28, 128 -> 256, stride 2, batch 128, training pass 85.6 / 83.8).
 // Products in us at 64 / 128: 2009 x 3664 x 8592 132.4 / 96.4, 1163 x 15776 x 8192
 // (256 x 256 tiles) 213.3 / 184.0; but 12760 x 3952 x 448 52.0 / 58.7 and 8660 x
 // 12508 x 304 (256) 101.8 / 109.1 (half a step), 15524 x 944 x 11328 (256) 153.7 /
@@ -664,15 +669,18 @@ bool carried_too_short(const IgemmBatch& b) {
 // the better form, with these limits 5%; 1x1 layers of 128 to 512 channels on
 // 256 x 256 tiles are 2 to 6% faster.
 constexpr int kHalfStep = 64;
-bool wide_steps(int K, int64_t tiles128, bool big) {
+bool wide_steps(int K, int64_t tiles128, bool big, bool conv) {
     const int tail = K % 128;   // bytes in the last step (0: a whole one)
     const bool half_empty = tail != 0 && tail <= kHalfStep;
+    const bool half_round = (tiles128 - 1) % 512 < 256;   // the last round leaves most CUs one workgroup
     if (tiles128 <= 256) return false;
+    if (conv) {
+        if (big) return K >= 2048;
+        if (K > 1024 && (half_round || (tiles128 < 384 && K < 2048))) return false;
+    }
     if (big) return tail != kHalfStep && K >= (half_empty ? 2048 : 640);
     if (tiles128 > 1536) return K >= (half_empty ? 1536 : 768);
-    // A last round that leaves most CUs one workgroup hides less behind the
-    // shallow ring; with misaligned rows as well the deep one wins.
-    if (tail == kHalfStep && (tiles128 - 1) % 512 < 256 && K >= 1024 && K < 4096) return false;
+    if (tail == kHalfStep && half_round && K >= 1024 && K < 4096) return false;
     return K >= 384;
 }
 
@@ -710,7 +718,7 @@ hipError_t run_mode(IgemmBatch& b, IgemmCtl ctl, hipStream_t stream) {
         tiles128 += (int64_t)((b.p[i].M + 127) / 128) * ((b.p[i].Nout + 127) / 128);
     }
     const bool big = maxN > 128 && work >= (int64_t)200 * 256 * 256 && tiles_of_256(b, maxK, tiles128);
-    const bool step128 = (MODE == kGemm || (MODE == kConv && whole128)) && maxN > 64 && wide_steps(maxK, tiles128, big);
+    const bool step128 = (MODE == kGemm || (MODE == kConv && whole128)) && maxN > 64 && wide_steps(maxK, tiles128, big, MODE == kConv);
     if constexpr (MODE == kGemm || MODE == kConv) {
         if (step128) {
             if (maxN <= 128) return launch_dma<128, 128, 2, 4, 2, 128, MODE>(b, ctl, stream);

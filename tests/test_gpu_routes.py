@@ -126,9 +126,14 @@ def test_ring_steps(case):
 
 @pytest.mark.parametrize("case", [
     ("fwd", 60, 28, 128, 256, 1, 1, 0, "128,128,4,4,2,64"),     # 368 x 2 tiles, 128 products per output
-    ("fwd", 60, 28, 128, 160, 3, 1, 1, "128,128,2,4,2,128"),
+    ("fwd", 60, 28, 128, 160, 3, 1, 1, "128,128,4,4,2,64"),     # 736: the second round leaves most CUs one
+    ("fwd", 70, 28, 128, 160, 3, 1, 1, "128,128,2,4,2,128"),    # 858
+    ("fwd", 128, 14, 256, 160, 3, 1, 1, "128,128,2,4,2,128"),   # 392
+    ("fwd", 120, 14, 128, 160, 3, 1, 1, "128,128,4,4,2,64"),    # 368: short, few CUs with two workgroups
+    ("fwd", 128, 14, 128, 160, 3, 1, 1, "128,128,2,4,2,128"),
     ("fwd", 80, 28, 512, 256, 1, 1, 0, "256,256,3,2,4,64"),
-    ("fwd", 80, 28, 640, 256, 1, 1, 0, "256,256,2,2,4,128"),
+    ("fwd", 80, 28, 1152, 256, 1, 1, 0, "256,256,3,2,4,64"),
+    ("fwd", 80, 28, 2048, 256, 1, 1, 0, "256,256,2,2,4,128"),
     ("fwd", 60, 28, 192, 160, 3, 1, 1, "128,128,4,4,2,64"),     # channels that are not whole 128s
 ], ids=str)
 def test_ring_steps_of_convolutions(case):
