@@ -690,7 +690,8 @@ bool wide_steps(int K, int64_t tiles128, bool big, bool conv) {
 // 256 35.5 us against 25.6, 28x28 192 -> 160 training pass 157 against 126).
 // Which are faster goes by rounds, 256 tiles or 512: by how far each overfills
 // its last one and pads the edges.  A round of 128 covers half the area of one
-// of 256 and takes about 1.7 K + 4000 where half the latter takes K + 4000.
+// of 256 and takes about 1.9 K + 4000 where half the latter takes K + 4000 (1.7
+// fits as well on average, but is more often far off for 128).
 // Products in us, tiles of 128 / 256 (rounds): 2321 x 5958 x 12352 231.7 / 154.8
 // (2, 1), 2819 x 10544 x 1136 73.9 / 53.6 (4, 2); but 3108 x 5008 x 9600 144.3 /
 // 206.4 (2, 2), 7235 x 6880 x 384 49.4 / 66.3 (7, 4).  Over 8400 random products
@@ -701,7 +702,7 @@ bool tiles_of_256(const IgemmBatch& b, int64_t K, int64_t tiles128) {
     for (int i = 0; i < b.nprob; i++)
         tiles256 += (int64_t)((b.p[i].M + 255) / 256) * ((b.p[i].Nout + 255) / 256);
     const int64_t r256 = (tiles256 + 255) / 256, r128 = (tiles128 + 511) / 512;
-    return 20 * r256 * (K + 4000) <= r128 * (17 * K + 40000);
+    return 20 * r256 * (K + 4000) <= r128 * (19 * K + 40000);
 }
 
 template <int MODE>

@@ -108,7 +108,7 @@ def test_small_product_rows(case):
     (16384, 2100, 752, "128,128,4,4,2,64"),      # 2176 tiles
     (16384, 2100, 768, "128,128,2,4,2,128"),
     (16384, 2100, 1072, "128,128,4,4,2,64"),     # the last step is half empty
-    (16384, 2100, 1552, "128,128,2,4,2,128"),
+    (16500, 1900, 1552, "128,128,2,4,2,128"),
     (16384, 1024, 624, "256,256,3,2,4,64"),      # tiles of 256
     (16384, 1024, 640, "256,256,2,2,4,128"),
     (16384, 1024, 1072, "256,256,3,2,4,64"),
@@ -116,8 +116,8 @@ def test_small_product_rows(case):
     (16384, 1024, 2112, "256,256,3,2,4,64"),     # odd multiple of 64
     (12800, 1100, 384, "256,256,3,2,4,64"),      # a round of 256 (padded) against two of 128
     (42000, 320, 320, "128,128,4,4,2,64"),       # two against two
-    (16384, 2100, 1584, "128,128,2,4,2,128"),    # three against five, short
-    (16384, 2100, 1600, "256,256,3,2,4,64"),     # and longer
+    (16384, 2100, 1136, "128,128,2,4,2,128"),    # three against five, short
+    (16384, 2100, 1152, "256,256,2,2,4,128"),    # and longer
 ], ids=str)
 def test_ring_steps(case):
     say("ring steps", case)
